@@ -65,17 +65,17 @@ template <typename T>
 __device__ __forceinline__ T from_next2(T x) { return from_next(from_next(x)); }
 
 // ---------------------------------------------------------------- reciprocals
-// Hardware reciprocal (square root) estimate refined by Newton steps: within
-// an ulp or two of the correctly rounded value, for the positive, finite,
-// normal arguments the scheme produces, at half the instructions of an IEEE
-// division.
+// Hardware reciprocal (square root) estimate refined by one step: within an
+// ulp or two of the correctly rounded value, for the positive, finite, normal
+// arguments the scheme produces, at half the instructions of an IEEE division.
+// In double the step is of third order (the estimate's relative error e, about
+// 5e-8, leaves e^3): one instruction less than two Newton steps for the
+// reciprocal, two less for the inverse square root.
 HWENO_HD double rcp_nr(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);          // 1/x = r / (1 - e)
+  return fma(r, fma(e, e, e), r);
 #else
   return 1.0 / x;
 #endif
@@ -90,11 +90,9 @@ HWENO_HD float rcp_nr(float x) {
 }
 HWENO_HD double rsqrt_nr(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  double y = __builtin_amdgcn_rsq(x);
-  // y <- y (3 - x y^2) / 2, twice
-  double h = 0.5 * x;
-  y = y * fma(-h * y, y, 1.5);
-  return y * fma(-h * y, y, 1.5);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);      // x^(-1/2) = y (1 - e)^(-1/2)
+  return fma(y * e, fma(0.375, e, 0.5), y);
 #else
   return 1.0 / sqrt(x);
 #endif
@@ -187,47 +185,88 @@ HWENO_HD void hweno_point(T um, T u0, T up, T vm, T vp, const Scheme& s,
 // ------------------------------------------------- HWENO-I, difference form
 // The forward stage kernels apply the same interpolation to the stencil's
 // differences, and carry every derivative multiplied by the mesh width of
-// its direction (v' = dx v, w' = dy w): then no constant of the
-// interpolation depends on the mesh. From e1 = u_i - u_{i-1},
+// its direction and by lam (v' = lam dx v, w' = lam dy w): then no constant
+// of the interpolation depends on the mesh. From e1 = u_i - u_{i-1},
 // e2 = u_{i+1} - u_i, S = v'_{i-1} + v'_{i+1}, D = v'_{i-1} - v'_{i+1} (a
 // linear map of the stencil, so for systems they are projected on the
 // characteristic basis in place of the five values, and u_i itself is never
 // projected) it returns the face corrections dR = u^-_{i+1/2} - u_i,
-// dL = u_i - u^+_{i-1/2} and h times the modified derivative, with the
-// arithmetic of hweno_point (there sv = S/4, dv = D/4). The smoothness
-// indicators, tau, epsilon, the weights and the combinations are evaluated
-// in double; q_l = beta_l + eps is formed directly (beta_1 = e1^2, ...).
+// dL = u_i - u^+_{i-1/2} and the modified derivative (point_vt_scale).
+// The kernels are bound by the number of instructions, FP64 and others alike,
+// hence the form of each expression:
+//   beta0: completing the squares of (GHYZ), with c = e1 + e2, s = e2 - e1 and
+//     S, D without the factor lam,
+//     beta0 = 3729/1280 (c - 299/339 S)^2 + 71/339 S^2
+//           + 266603/1680 (s + 263845/533206 D)^2 + 1421461/5332060 D^2;
+//     in FP64 lam = kLam, kLam^2 = 71/339, makes the weight of the carried S^2
+//     one;
+//   weights: o_l = P + tau P / q_l with P = q0 q1 q2 (see hweno_point); the
+//     normalisations are used divided by gamma0 and d0, which the constants of
+//     the numerators absorb;
+//   factors that a later FMA can take are left out of the combinations.
+// 51 instructions against 59 for the direct form with two Newton steps in the
+// reciprocal. With the other reorderings of the same kind (face_derivs_diff,
+// Euler::jac, interface_flux) a row iteration of the FP64 2D Euler stage kernel
+// went from 1555 to 1408 VALU instructions, that of the interface basis from
+// 2826 to 2371, FP32's from 1490 to 1418: 2048^2, two steps, 2.05 -> 1.99 ms
+// (there the chip is at its power limit: 1400 W, 2.05 GHz), FP32 one step 0.737
+// -> 0.702 ms, interface basis 1000x777 0.729 -> 0.661 ms. The smoothness indicators, tau, epsilon, the weights and the
+// combinations are evaluated in double; q_l = beta_l + eps is formed directly.
+// What FP32 does in float (everything outside hweno_point_diff) keeps the
+// textbook scaling and order of operations, lam = 1: each reordering there
+// moves the rounding of its results at the 1e-7 level, that of the time step
+// with them.
+constexpr double kLam = 0.45764563586207049;     // sqrt(71/339)
+// Scales of the carried derivatives: lam h v at the cells, mu lam h v at the
+// faces.
+template <typename T>
+struct Carried {
+  static constexpr double lam = sizeof(T) == 4 ? 1.0 : kLam;
+  static constexpr double mu = sizeof(T) == 4 ? 1.0 : 16.0;
+};
 struct PointK {
-  double eps, gamma0, g1, d0, d1;
-  double K, hg1, A;    // 11/32 - g1/2, g1/2, 3/4 - d1
+  double eps;
+  double rho, rhod;        // g1 / gamma0, d1 / d0
+  double K, Ks;            // of the face values: c and S, over gamma0
+  double m, X;             // s + ..D and X, over gamma0
+  double Ac, At, Xt;       // of the modified derivative: c, S and X
 };
 
-HWENO_HD PointK point_k(const Scheme& s) {
+// vts: the scale of the modified derivative (point_vt_scale).
+HWENO_HD PointK point_k(const Scheme& s, double lam, double vts) {
   PointK k;
   k.eps = s.eps;
-  k.gamma0 = s.gamma0;
-  k.g1 = s.g1;
-  k.d0 = s.d0;
-  k.d1 = s.d1;
-  k.K = 0.34375 - 0.5 * s.g1;
-  k.hg1 = 0.5 * s.g1;
-  k.A = 0.75 - s.d1;
+  k.rho = s.g1 / s.gamma0;
+  k.rhod = s.d1 / s.d0;
+  k.K = (0.34375 - 0.5 * s.g1) / s.gamma0;
+  k.Ks = -0.09375 / (lam * s.gamma0);
+  k.m = 0.21875 / s.gamma0;
+  k.X = 0.5 * s.g1 / s.gamma0;
+  k.Ac = (0.75 - s.d1) / (s.d0 * vts);
+  k.At = -0.25 / (lam * s.d0 * vts);
+  k.Xt = s.d1 / (s.d0 * vts);
   return k;
+}
+// The modified derivative returned by hweno_point_diff is h v~ over this scale:
+// in FP64 the one that makes the weight Ac of c one.
+template <typename T>
+HWENO_HD double point_vt_scale(const Scheme& s) {
+  return sizeof(T) == 8 ? (0.75 - s.d1) / s.d0 : 1.0;
 }
 
 template <typename T>
 HWENO_HD void hweno_point_diff(T e1_, T e2_, T S_, T D_, const PointK& k, T& dR, T& dL, T& vt) {
-  constexpr double r13 = 2.0816659994661326;    // sqrt(13/3)
-  constexpr double r781 = 6.248999919987197;    // sqrt(781/20)
-  constexpr double r1421 = 24.99636017459386;   // sqrt(1421461/2275)
   const double e1 = (double)e1_, e2 = (double)e2_, S = (double)S_, D = (double)D_;
-  const double cdf = e1 + e2, sdf = e2 - e1;
-  // (GHYZ) closed form with the weights' square roots folded in
-  const double t1 = fma(0.6875, cdf, -0.1875 * S);
-  const double t2 = fma(r13 * 197.0 / 260.0, sdf, (r13 * 67.0 / 520.0) * D);
-  const double a3 = fma(-0.25 * r781, cdf, (0.25 * r781) * S);
-  const double a4 = fma(-0.5 * r1421, sdf, (-0.25 * r1421) * D);
-  const double q0 = fma(t1, t1, fma(t2, t2, fma(a3, a3, fma(a4, a4, k.eps))));
+  constexpr double lam = Carried<T>::lam;
+  const double c = e1 + e2, s = e2 - e1;
+  const double u = fma(-299.0 / 339.0 / lam, S, c);
+  const double w = fma(263845.0 / 533206.0 / lam, D, s);
+  double qS;
+  if constexpr (lam == 1.0) qS = fma((71.0 / 339.0) * S, S, k.eps);
+  else qS = fma(S, S, k.eps);
+  const double q0 = fma((266603.0 / 1680.0) * w, w,
+                        fma((3729.0 / 1280.0) * u, u,
+                            fma((1421461.0 / 5332060.0 / (lam * lam)) * D, D, qS)));
   const double q1 = fma(e1, e1, k.eps), q2 = fma(e2, e2, k.eps);
   // (nonlinear), scaled by q0 q1 q2: o_l = P + tau P / q_l
   const double ts = fabs(q0 - q1) + fabs(q0 - q2);
@@ -236,30 +275,37 @@ HWENO_HD void hweno_point_diff(T e1_, T e2_, T S_, T D_, const PointK& k, T& dR,
   const double P = A * q0;
   const double o0 = fma(A, tau, P), o1 = fma(B, tau, P), o2 = fma(C, tau, P);
   const double o12 = o1 + o2;
-  const double Sg = fma(k.gamma0, o0, k.g1 * o12);
-  const double Sd = fma(k.d0, o0, k.d1 * o12);
+  const double Sg = fma(k.rho, o12, o0), Sd = fma(k.rhod, o12, o0);
   const double inv = rcp_nr(Sg * Sd);
   const double iSg = Sd * inv, iSd = Sg * inv;
   // (interp) and its mirror image, (limiter)
   const double X = fma(o1, e1, o2 * e2);
-  const double base = fma(k.K, cdf, -0.09375 * S);
-  const double m = fma(0.21875, sdf, 0.046875 * D);
-  const double P1 = fma(o0, base, k.hg1 * X), P2 = o0 * m;
-  dR = (T)((P1 + P2) * iSg);
-  dL = (T)((P1 - P2) * iSg);
-  const double AT = fma(k.A, cdf, -0.25 * S);
-  vt = (T)(fma(o0, AT, k.d1 * X) * iSd);
+  const double base = fma(k.K, c, k.Ks * S);
+  const double om = o0 * fma(3.0 / 14.0 / lam, D, s);
+  const double N = fma(k.X, X, o0 * base);
+  dR = (T)(fma(k.m, om, N) * iSg);
+  dL = (T)(fma(-k.m, om, N) * iSg);
+  double At;
+  if constexpr (sizeof(T) == 8) At = fma(k.At, S, c);
+  else At = fma(k.At, S, k.Ac * c);
+  vt = (T)(fma(o0, At, k.Xt * X) * iSd);
 }
 
-// (P'xi) and its mirror through the same differences, times h (linear, so
-// valid in conserved or characteristic variables):
+// (P'xi) and its mirror through the same differences (linear, so valid in
+// conserved or characteristic variables):
 //   h v^-_{i+1/2} = -3/16 e1 + 21/16 e2 - S/16 + D/8,
-//   h v^+_{i-1/2} = 21/16 e1 - 3/16 e2 - S/16 - D/8.
+//   h v^+_{i-1/2} = 21/16 e1 - 3/16 e2 - S/16 - D/8   (S, D without kLam);
+// in FP64 times 16 kLam.
 template <typename T>
 HWENO_HD void face_derivs_diff(T e1, T e2, T S, T D, T& vR, T& vL) {
-  const T s = T(-0.0625) * S;
-  vR = fma(T(-0.1875), e1, fma(T(1.3125), e2, fma(T(0.125), D, s)));
-  vL = fma(T(1.3125), e1, fma(T(-0.1875), e2, fma(T(-0.125), D, s)));
+  if constexpr (sizeof(T) == 8) {
+    vR = fma(T(-3.0 * kLam), e1, fma(T(21.0 * kLam), e2, fma(T(2), D, -S)));
+    vL = fma(T(21.0 * kLam), e1, fma(T(-3.0 * kLam), e2, fma(T(-2), D, -S)));
+  } else {
+    const T s = T(-0.0625) * S;
+    vR = fma(T(-0.1875), e1, fma(T(1.3125), e2, fma(T(0.125), D, s)));
+    vL = fma(T(1.3125), e1, fma(T(-0.1875), e2, fma(T(-0.125), D, s)));
+  }
 }
 
 // (P'xi) and its mirror: v^-_{i+1/2} = p0'(x_{i+1/2}), v^+_{i-1/2} = p0'(x_{i-1/2}).
@@ -405,13 +451,38 @@ struct Euler {
     }
   }
   // A(U) V by the chain rule through the primitives: with d(.) the derivative
-  // along V, du = (V1 - u V0)/rho, dv = (V2 - v V0)/rho and
-  // dP = (gas-1)(V_E - u V1 - v V2 + k V0).
+  // along V, a = V1 - u V0 = rho du, b = V2 - v V0 = rho dv and
+  // dP = (gas-1)(V_E - u V1 - v V2 + k V0). The terms rho u du = u a and
+  // du (E + P) = a H need no division by rho in FP64's order; FP32 keeps the
+  // order with du, dv (see hweno_point_diff).
   template <int D, typename T>
   HWENO_HD void jac(const T (&U)[NC], const Prim<T>& q, const T (&V)[NC],
                                       T (&O)[NC]) const {
     const T gm1 = T(gas - 1.0);
-    if constexpr (DIM == 1) {
+    if constexpr (sizeof(T) == 8) {
+      const T H = q.Ep * q.ir;
+      const T a = fma(-q.mu, V[0], V[1]);
+      if constexpr (DIM == 1) {
+        const T dP = gm1 * fma(q.k, V[0], fma(-q.mu, V[1], V[2]));
+        O[0] = V[1];
+        O[1] = fma(q.mu, V[1] + a, dP);
+        O[2] = fma(a, H, q.mu * (V[2] + dP));
+      } else {
+        const T b = fma(-q.nu, V[0], V[2]);
+        const T dP = gm1 * fma(q.k, V[0], fma(-q.nu, V[2], fma(-q.mu, V[1], V[3])));
+        if constexpr (D == 0) {
+          O[0] = V[1];
+          O[1] = fma(q.mu, V[1] + a, dP);
+          O[2] = fma(q.nu, V[1], q.mu * b);
+          O[3] = fma(a, H, q.mu * (V[3] + dP));
+        } else {
+          O[0] = V[2];
+          O[1] = fma(q.mu, V[2], q.nu * a);
+          O[2] = fma(q.nu, V[2] + b, dP);
+          O[3] = fma(b, H, q.nu * (V[3] + dP));
+        }
+      }
+    } else if constexpr (DIM == 1) {
       const T du = (V[1] - q.mu * V[0]) * q.ir;
       const T dP = gm1 * (V[2] - q.mu * V[1] + q.k * V[0]);
       O[0] = V[1];
@@ -598,6 +669,25 @@ struct Euler {
     e.nuc = e.q.nu * e.c;
     return e;
   }
+  // The cell_eig form of Roe's basis of the states UL, UR (its primitives but
+  // the velocities and k are not set).
+  template <typename T>
+  HWENO_HD CellEig<T> roe_cell_eig(const T (&UL)[NC], const T (&UR)[NC]) const {
+    const Eig<T> r = roe_eig(UL, UR);
+    CellEig<T> e;
+    e.q = {};
+    e.q.mu = r.mu;
+    e.q.nu = r.nu;
+    e.q.k = r.k;
+    e.c = r.c;
+    e.H = r.H;
+    e.b1h = T(0.5) * r.b1;
+    e.b2h = T(0.5) * r.b2;
+    e.ich = T(0.5) * r.ic;
+    e.muc = r.mu * r.c;
+    e.nuc = r.nu * r.c;
+    return e;
+  }
   // w = L x (the same L as project): with s' = s/2 and t' = t/2,
   // w = (s' + t', x0 - 2 s', x2 - v x0 | x1 - u x0, s' - t').
   template <int D, typename T>
@@ -666,10 +756,14 @@ struct Euler {
     const double c = c2 * rsqrt_nr(c2);
     sx = fabs(mu) + c;
     sy = fabs(nu) + c;
+    // any non-finite value makes p non-finite; which flag it is matters only
+    // where one is raised
     unsigned f = 0;
+    if (!(r > 0.0 && p > 0.0 && p < __builtin_huge_val())) {
 #pragma unroll
-    for (int k = 0; k < NC; ++k) f |= isfinite((double)U[k]) ? 0u : 1u;
-    if (!(r > 0.0) || !(p > 0.0)) f |= 2u;
+      for (int k = 0; k < NC; ++k) f |= isfinite((double)U[k]) ? 0u : 1u;
+      if (!(r > 0.0) || !(p > 0.0)) f |= 2u;
+    }
     return f;
   }
   template <typename T>
@@ -780,9 +874,9 @@ HWENO_HD void hweno_cell(const Sys& sy, const Scheme& s, double h, double ih,
 // HWENO-I on one cell in direction D, difference form (forward kernels): from
 // the conserved-variable differences E1 = U_i - U_{i-1}, E2 = U_{i+1} - U_i
 // and the sums S = A'_{i-1} + A'_{i+1}, Dd = A'_{i-1} - A'_{i+1} of the
-// derivative along D times the mesh width (A' = h A), it returns u at both
-// faces, h times the modified derivative and h times the face derivatives of
-// (P'xi). Systems project the four differences on the cell's characteristic
+// carried derivative along D (A' = lam h A), it returns u at both faces, the
+// modified derivative as hweno_point_diff scales it and the face derivatives
+// of (P'xi) as face_derivs_diff does. Systems project the four differences on the cell's characteristic
 // basis (remarks on the local characteristic decomposition in sections 2 and
 // 3), interpolate every characteristic variable and project the corrections
 // back onto U_i; the face derivatives are linear and taken component-wise.
@@ -815,6 +909,41 @@ HWENO_HD void hweno_cell_diff(const Sys& sy, const PointK& k,
     sy.template unproject_add<D, true>(ce, cl, U0, uL);
     sy.template unproject_add<D, false>(ce, ct, (const T*)nullptr, at);
   }
+}
+
+// The same with the interface-basis switch (see hweno_cell_iface): each of the
+// three outputs from its own basis, so three applications, each keeping one
+// output. In FP64; FP32 keeps hweno_cell_iface (see hweno_point_diff).
+template <int D, class Sys, typename T>
+HWENO_HD void hweno_cell_diff_iface(const Sys& sy, const PointK& k,
+                                    const typename Sys::template CellEig<T>& ce,
+                                    const T (&Um)[Sys::NC], const T (&U0)[Sys::NC],
+                                    const T (&Up)[Sys::NC], const T (&E1)[Sys::NC],
+                                    const T (&E2)[Sys::NC], const T (&S)[Sys::NC],
+                                    const T (&Dd)[Sys::NC], T (&uR)[Sys::NC], T (&uL)[Sys::NC],
+                                    T (&at)[Sys::NC], T (&vR)[Sys::NC], T (&vL)[Sys::NC]) {
+  constexpr int NC = Sys::NC;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) face_derivs_diff(E1[c], E2[c], S[c], Dd[c], vR[c], vL[c]);
+  auto apply = [&](const auto& e, int which, T (&out)[NC]) {
+    T e1[NC], e2[NC], sc[NC], dc[NC], c[NC];
+    sy.template project_half<D>(e, E1, e1);
+    sy.template project_half<D>(e, E2, e2);
+    sy.template project_half<D>(e, S, sc);
+    sy.template project_half<D>(e, Dd, dc);
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      T r_, l_, t_;
+      hweno_point_diff<T>(e1[j], e2[j], sc[j], dc[j], k, r_, l_, t_);
+      c[j] = which == 0 ? r_ : (which == 1 ? l_ : t_);
+    }
+    if (which == 0) sy.template unproject_add<D, false>(e, c, U0, out);
+    else if (which == 1) sy.template unproject_add<D, true>(e, c, U0, out);
+    else sy.template unproject_add<D, false>(e, c, (const T*)nullptr, out);
+  };
+  apply(sy.roe_cell_eig(U0, Up), 0, uR);
+  apply(sy.roe_cell_eig(Um, U0), 1, uL);
+  apply(ce, 2, at);
 }
 
 // ------------------------------------------------------------- index maps

@@ -64,6 +64,16 @@ struct StepCtl {
   double cfl, dt_fixed, t_end, hx, hy;
 };
 
+// Scales between what the stage kernels carry and the scheme's quantities: a
+// row's derivatives are multiplied by lx = lam dx, ly = lam dy when it is
+// loaded (Carried); ilx, ily their inverses; vtx, vty times the modified
+// derivatives of the interpolation give v~, w~; xu, xv, xw times the
+// differences F_{i-1/2} - F_{i+1/2} of the scaled interface fluxes
+// (interface_flux) along x give L of the three equations, yu, yv, yw along y.
+struct FluxK {
+  double lx, ly, ilx, ily, vtx, vty, xu, xv, xw, yu, yv, yw;
+};
+
 template <typename T>
 struct StageArgs {
   const T* U;  const T* V;  const T* W;   // stage state X (W null in 1D)
@@ -88,6 +98,7 @@ struct StageArgs {
   StepCtl ctl;                            // stage 1 computing dt, stages 2-3 of such a step
   Scheme s;
   PointK pk;                              // HWENO point constants (difference form)
+  FluxK fk;
 };
 
 // Start of a stage launch: the stage's dt and time, and whether the step is
@@ -206,23 +217,41 @@ __device__ __forceinline__ void atomic_max_pos(unsigned long long* p, double v) 
 }
 
 // ------------------------------------------------------ x-direction sweep
-// (Cd-1)-(DfDh) at one interface, with the derivative fluxes carried times
-// the mesh width h (h' = h f'(u) v): D(f) and h D(h).
+// The numerical fluxes (flux-1d), (flux-LF) with the central correction
+// (Cd-1)-(DfDh) at one interface x_{i+1/2}, from the pointwise fluxes as f0 =
+// f_i and the differences d0 = f_i - f_{i-1}, d1, d2 (FP64) or the values fm,
+// f0, f1, f2 at i-1 .. i+2 (FP32, d unused), the pointwise derivative fluxes
+// hm = h'_{i-1}, hp = h'_{i+2} (h' = lam h f'(u) v), and the sums sF, sH of
+// the LF terms f + a u of the two sides (those of the derivative equation
+// carry mu besides). In FP64 scaled so that every term costs one FMA or none:
+//   F = -960 lam / 19 f_{i+1/2},   H = 864 / 37 (lam h) h_{i+1/2};
+// in FP32 (kFluxScaled false) F = f_{i+1/2}, H = h h_{i+1/2}.
 template <typename T>
-__device__ __forceinline__ void central_corr_k(T fm1, T f0, T fp1, T fp2, T hm1, T hp2, T& Df,
-                                               T& Dh) {
-  const T s4 = (fm1 + fp2) - (f0 + fp1);
-  Df = fma(T(-97.0 / 1920.0), s4, T(-19.0 / 960.0) * (hm1 - hp2));
-  Dh = fma(T(697.0 / 5184.0), fm1 - fp2, fma(T(-61.0 / 192.0), f0 - fp1, T(37.0 / 864.0) * (hm1 + hp2)));
+constexpr bool kFluxScaled = sizeof(T) == 8;
+template <typename T>
+__device__ __forceinline__ void interface_flux(T d0, T d1, T d2, T hm, T hp, T sF, T sH, T& F, T& H) {
+  constexpr double lam = Carried<T>::lam, mu = Carried<T>::mu;
+  F = fma(T(-480.0 / 19.0 * lam), sF, fma(T(97.0 / 38.0 * lam), d2 - d0, hm - hp));
+  H = fma(T(432.0 / 37.0 / mu), sH,
+          fma(T(475.0 / 111.0 * lam), d1, fma(T(-697.0 / 222.0 * lam), d0 + d2, hm + hp)));
+}
+template <typename T>
+__device__ __forceinline__ void interface_flux_plain(T fm, T f0, T f1, T f2, T hm, T hp, T sF, T sH,
+                                                     T& F, T& H) {
+  const T s4 = (fm + f2) - (f0 + f1);
+  const T Df = fma(T(-97.0 / 1920.0), s4, T(-19.0 / 960.0) * (hm - hp));
+  const T Dh = fma(T(697.0 / 5184.0), fm - f2, fma(T(-61.0 / 192.0), f0 - f1, T(37.0 / 864.0) * (hm + hp)));
+  F = fma(T(0.5), sF, Df);
+  H = fma(T(0.5), sH, Dh);
 }
 
 // Steps 1-4 of section 2 along x for the row held by the wavefront (one cell
-// per lane). Inputs: this lane's U, V' = dx u_x and, with NF == 3,
-// W' = dy u_y (derivatives carried times their mesh width, see
-// hweno_cell_diff), and the cell's characteristic basis and primitives
-// `ce`. Outputs: the residual parts -(F_{i+1/2} - F_{i-1/2})/dx of the u-,
-// v- and w-equations (the last from the mixed flux eta = f'(u) w),
-// accumulated in double and unscaled, and dx v~. Valid on lanes 2..61.
+// per lane). Inputs: this lane's U, V' = lam dx u_x and, with NF == 3,
+// W' = lam dy u_y (carried derivatives, see hweno_cell_diff), and the cell's
+// characteristic basis and primitives `ce`. Outputs: the differences
+// F_{i-1/2} - F_{i+1/2} of the scaled fluxes of the u-, v- and w-equations
+// (the last 12 times the mixed flux of eta = f'(u) w'), formed in double, and
+// the modified derivative as hweno_cell_diff scales it. Valid on lanes 2..61.
 template <int NF, bool IFACE, class Sys, typename T>
 __device__ __forceinline__ void sweep_x(const Sys& sy, const Scheme& s, const PointK& pk,
                                         double alpha,
@@ -235,7 +264,7 @@ __device__ __forceinline__ void sweep_x(const Sys& sy, const Scheme& s, const Po
   // Step 1: HWENO once per cell -> u at both faces, v~ at the centre, and the
   // face derivatives of (P'xi)
   T uR[NC], uL[NC], vR[NC], vL[NC];
-  if constexpr (IFACE) {
+  if constexpr (IFACE && sizeof(T) == 4) {
     T Um[NC], Up[NC], Vm[NC], Vp[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -261,7 +290,17 @@ __device__ __forceinline__ void sweep_x(const Sys& sy, const Scheme& s, const Po
       Sv[c] = vm + vp;
       Dv[c] = vm - vp;
     }
-    hweno_cell_diff<0>(sy, pk, ce, U, E1, E2, Sv, Dv, uR, uL, vt, vR, vL);
+    if constexpr (IFACE) {
+      T Um[NC], Up[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        Um[c] = from_prev(U[c]);
+        Up[c] = from_next(U[c]);
+      }
+      hweno_cell_diff_iface<0>(sy, pk, ce, Um, U, Up, E1, E2, Sv, Dv, uR, uL, vt, vR, vL);
+    } else {
+      hweno_cell_diff<0>(sy, pk, ce, U, E1, E2, Sv, Dv, uR, uL, vt, vR, vL);
+    }
   }
   // pointwise f, h' = f'(u) v', eta' = f'(u) w' at the cell centre
   T f[NC], hf[NC], e[NC];
@@ -288,42 +327,47 @@ __device__ __forceinline__ void sweep_x(const Sys& sy, const Scheme& s, const Po
       pH[c] = fma(-a, vL[c], hl[c]);
     }
   }
-  // Steps 2-3 at x_{i+1/2}, then Step 4; the v-equation's fluxes carry a
-  // factor dx, eta' a factor dy, removed in the flux differences
-  const double cv = s.idx * s.idx, cw = s.idx * s.idy * (1.0 / 12.0);
+  // Steps 2-3 at x_{i+1/2}, then the differences of Step 4
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    const T fm1 = from_prev(f[c]), fp1 = from_next(f[c]), fp2 = from_next(fp1);
-    const T hm1 = from_prev(hf[c]), hp1 = from_next(hf[c]), hp2 = from_next(hp1);
-    T Df, Dh;
-    central_corr_k(fm1, f[c], fp1, fp2, hm1, hp2, Df, Dh);
-    const T Fi = fma(T(0.5), mF[c] + from_next(pF[c]), Df);
-    const T Hi = fma(T(0.5), mH[c] + from_next(pH[c]), Dh);
-    RU[c] = ((double)from_prev(Fi) - (double)Fi) * s.idx;
-    RV[c] = ((double)from_prev(Hi) - (double)Hi) * cv;
+    T Fi, Hi;
+    const T sF = mF[c] + from_next(pF[c]), sH = mH[c] + from_next(pH[c]);
+    if constexpr (kFluxScaled<T>) {
+      const T d0 = f[c] - from_prev(f[c]), d1 = from_next(d0), d2 = from_next(d1);
+      interface_flux(d0, d1, d2, from_prev(hf[c]), from_next2(hf[c]), sF, sH, Fi, Hi);
+    } else {
+      const T fp = from_next(f[c]);
+      interface_flux_plain(from_prev(f[c]), f[c], fp, from_next(fp), from_prev(hf[c]),
+                           from_next2(hf[c]), sF, sH, Fi, Hi);
+    }
+    RU[c] = (double)from_prev(Fi) - (double)Fi;
+    RV[c] = (double)from_prev(Hi) - (double)Hi;
     if constexpr (NF == 3) {
       // (mixed) times 12: 7 (e_i + e_{i+1}) - (e_{i-1} + e_{i+2})
       const T em1 = from_prev(e[c]), ep1 = from_next(e[c]), ep2 = from_next(ep1);
       const T Ei = fma(T(7), e[c] + ep1, -(em1 + ep2));
-      RW[c] = ((double)from_prev(Ei) - (double)Ei) * cw;
+      RW[c] = (double)from_prev(Ei) - (double)Ei;
     }
   }
 }
 
-// The Runge-Kutta combination (fully-hweno)/(2Dfully-hweno) of one value,
-// written as a part known before the y-sweep's flux difference L_y and the
-// weight of L_y: X_new = rk_part + rk_wl dt L_y, with
-//   stage 1: X + dt L_x,  stage 2: 3/4 B + 1/4 (X + dt L_x),
-//   stage 3: 1/3 B + 2/3 (X + dt L_x),  operator only (rhs): L_x.
-// All in double, one rounding at the store. The stage-3 weights multiply (an
-// FP64 division would cost about ten instructions per value).
+// The Runge-Kutta combination (fully-hweno)/(2Dfully-hweno) of one value, in
+// two parts: X_new = rk_base + rk_wl dt L, with
+//   stage 1: X + dt L,  stage 2: 3/4 B + 1/4 (X + dt L),
+//   stage 3: 1/3 B + 2/3 (X + dt L),  operator only (rhs): L.
+// X is x times `scale` (1, or the scale of a modified derivative). All in
+// double, one rounding at the store. The stage-3 weights multiply (an FP64
+// division would cost about ten instructions per value).
 template <int MODE>
-__device__ __forceinline__ double rk_part(double x, double base, double dt, double Lx) {
-  if constexpr (MODE == kStage1) return fma(dt, Lx, x);
-  else if constexpr (MODE == kStage2) return fma(0.25 * dt, Lx, fma(0.25, x, 0.75 * base));
-  else if constexpr (MODE == kStage3)
-    return fma((2.0 / 3.0) * dt, Lx, fma(2.0 / 3.0, x, (1.0 / 3.0) * base));
-  else return Lx;
+__device__ __forceinline__ double rk_x(double scale) {
+  return MODE == kStage2 ? 0.25 * scale : (MODE == kStage3 ? (2.0 / 3.0) * scale : scale);
+}
+template <int MODE>
+__device__ __forceinline__ double rk_base(double x, double wx, double base) {
+  if constexpr (MODE == kStage1) return wx * x;
+  else if constexpr (MODE == kStage2) return fma(wx, x, 0.75 * base);
+  else if constexpr (MODE == kStage3) return fma(wx, x, (1.0 / 3.0) * base);
+  else return 0.0;
 }
 template <int MODE>
 __device__ __forceinline__ double rk_wl(double dt) {
@@ -363,15 +407,16 @@ __global__ __launch_bounds__(64) void stage1d_kernel(StageArgs<T> A, Sys sy) {
       }
     }
   }
-  // derivatives carried times dx (see sweep_x)
+  // the carried derivatives (see sweep_x)
 #pragma unroll
-  for (int c = 0; c < NC; ++c) V[c] = T(A.s.dx) * V[c];
+  for (int c = 0; c < NC; ++c) V[c] = T(A.fk.lx) * V[c];
   double RU[NC], RV[NC], RW[NC];
   T vt[NC];
   const auto ce = sy.cell_eig(U);
   sweep_x<2, IFACE>(sy, A.s, A.pk, ax, ce, U, V, W, RU, RV, RW, vt);
   double smax = 0.0;
   unsigned flag = 0;
+  const double wl = rk_wl<MODE>(dt), wu = wl * A.fk.xu, wv = wl * A.fk.xv;
   if (out) {
     T Un[NC];
 #pragma unroll
@@ -379,11 +424,10 @@ __global__ __launch_bounds__(64) void stage1d_kernel(StageArgs<T> A, Sys sy) {
       const int o = c * A.plane + col;
       const double ub = MODE >= kStage2 ? (double)A.Ub[o] : 0.0;
       const double vb = MODE >= kStage2 ? (double)A.Vb[o] : 0.0;
-      const double vtc = (double)vt[c] * A.s.idx;
-      Un[c] = (T)rk_part<MODE>((double)U[c], ub, dt, RU[c]);
+      Un[c] = (T)fma(wu, RU[c], rk_base<MODE>((double)U[c], rk_x<MODE>(1.0), ub));
       A.Uo[o] = Un[c];
-      A.Vo[o] = (T)rk_part<MODE>(vtc, vb, dt, RV[c]);
-      if (MODE == kStage1 || MODE == kRhs) A.Vt[o] = (T)vtc;
+      A.Vo[o] = (T)fma(wv, RV[c], rk_base<MODE>((double)vt[c], rk_x<MODE>(A.fk.vtx), vb));
+      if (MODE == kStage1 || MODE == kRhs) A.Vt[o] = (T)((double)vt[c] * A.fk.vtx);
     }
     if (A.alpha_next) {
       double sy_;
@@ -439,7 +483,7 @@ __device__ __forceinline__ void load_row(const StageArgs<T>& A, double tstage, i
 
 // What load_row leaves to the row's first use (so that the loads stay in
 // flight until then): the ghost rules of walls, fixed states and split sides,
-// and the derivatives times their mesh width (see sweep_x).
+// and the scales of the carried derivatives (see sweep_x).
 template <class Sys, bool WALLS, typename T>
 __device__ __forceinline__ void finish_row(const StageArgs<T>& A, int r, bool xwall, bool xm,
                                            int xf, int split_rule, T (&U)[Sys::NC],
@@ -478,8 +522,8 @@ __device__ __forceinline__ void finish_row(const StageArgs<T>& A, int r, bool xw
   }
 #pragma unroll
   for (int c = 0; c < Sys::NC; ++c) {
-    V[c] = T(A.s.dx) * V[c];
-    W[c] = T(A.s.dy) * W[c];
+    V[c] = T(A.fk.lx) * V[c];
+    W[c] = T(A.fk.ly) * W[c];
   }
 }
 
@@ -528,12 +572,12 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
   const int y1 = min(y0 + A.rows, A.ny);
   const double ax = A.alpha[0], ay = A.alpha[1];
   const T a_y = T(ay);
-  // weights of the y flux differences (fprev - F) in the new state: the
-  // stage's weight of dt L times 1/dy (and 1/(12 dy) for the mixed flux,
-  // which is carried times 12)
-  const double wl = rk_wl<MODE>(dt) * s.idy;
-  // the v-equation's y-fluxes carry 12 dx, the w-equation's dy
-  const double wlv = wl * s.idx * (1.0 / 12.0), wlw = wl * s.idy;
+  // weights of the flux differences (F_{i-1/2} - F_{i+1/2}) of the three
+  // equations in the new state, along x and y, and of the modified derivatives
+  const double wl = rk_wl<MODE>(dt);
+  const double wxu = wl * A.fk.xu, wxv = wl * A.fk.xv, wxw = wl * A.fk.xw;
+  const double wyu = wl * A.fk.yu, wyv = wl * A.fk.yv, wyw = wl * A.fk.yw;
+  const double wvt = rk_x<MODE>(A.fk.vtx), wwt = rk_x<MODE>(A.fk.vty);
 
   // Rows march upwards; at iteration r the rows r-2, r-1 (registers) and r
   // (just loaded) are present. Iteration r does: the pointwise y-fluxes of
@@ -542,14 +586,25 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
   // row r-2; the x-sweep of row r-1, whose flux difference and RK
   // combination wait in LDS (pend) until the next iteration adds the
   // y-part. U, W of rows r-2, r-1 and V of row r-1 stay in registers.
-  T Ua[NC], Ub[NC], Wa[NC], Wb[NC], Vb[NC];
-  // pointwise g, theta, xi of rows r-3, r-2, r-1, slot (row mod 3); each
-  // lane only touches its own column
+  T Ub[NC], Wb[NC], Vb[NC];
+  // U, W of row r-2 and the pointwise g of row r-1: in LDS in FP64 (4 blocks
+  // of 40 KB a CU; in registers their moves to AGPRs cost more than the LDS
+  // accesses), in registers in FP32 (8 blocks of 20 KB)
+  constexpr bool kRowLds = sizeof(T) == 8 && !IFACE && !SOURCE;
+  __shared__ T rowl[kRowLds ? 3 : 1][kRowLds ? NC : 1][kWave];
+  T rowr[kRowLds ? 1 : 3][kRowLds ? 1 : NC];
+  auto prev_row = [&](int f, int c) -> T& {
+    if constexpr (kRowLds) return rowl[f][c][lane];
+    else return rowr[f][c];
+  };
+  // pointwise g (FP64: the difference g_k - g_{k-1}), theta, xi of rows k =
+  // r-3, r-2, r-1, slot (row mod 3); each lane only touches its own column
   __shared__ T ring[3][3][NC][kWave];
   int slot = ((y0 - 2) % 3 + 3) % 3;     // slot of row r (and of row r-3)
   // Lax-Friedrichs sums g(u) + a u, theta + a w at the top face of row r-2
   __shared__ T topr[2][NC][kWave];
-  // y-interface fluxes g, theta, 12 xi at (r-3)+1/2
+  // y-interface fluxes of the u-, w- and v-equation at (r-3)+1/2, scaled as
+  // interface_flux does (the mixed one times 12)
   __shared__ T fprev[3][NC][kWave];
   // RK combination of row r-2 (u, v, w) without its y flux difference
   __shared__ double pend[3][NC][kWave];
@@ -563,8 +618,10 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
   // the compiler can schedule across): start from an admissible state.
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    Ua[c] = Ub[c] = T(c == 0 ? 1.0 : (c == NC - 1 ? 2.0 : 0.0));
-    Wa[c] = Wb[c] = Vb[c] = T(0);
+    Ub[c] = T(c == 0 ? 1.0 : (c == NC - 1 ? 2.0 : 0.0));
+    Wb[c] = Vb[c] = T(0);
+    prev_row(0, c) = Ub[c];
+    prev_row(1, c) = prev_row(2, c) = T(0);
   }
   int rule_n;
   load_row<Sys, WALLS>(A, tstage, y0 - 2, col, gcol, Un, Vn, Wn, rule_n);
@@ -602,7 +659,15 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
     {
       ce = sy.cell_eig(Ub);
       T uT[NC], uB[NC], wT[NC], wB[NC];
-      if constexpr (IFACE) {
+      T Ua[NC], Wa[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        Ua[c] = prev_row(0, c);
+        Wa[c] = prev_row(1, c);
+        prev_row(0, c) = Ub[c];
+        prev_row(1, c) = Wb[c];
+      }
+      if constexpr (IFACE && sizeof(T) == 4) {
         // mesh width 1 for the scaled derivatives
         hweno_cell_b<1, true>(sy, s, 1.0, 1.0, ce.q, Ua, Ub, Uc, Wa, Wc, uT, uB, wt);
 #pragma unroll
@@ -616,7 +681,10 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
           Sw[c] = Wa[c] + Wc[c];
           Dw[c] = Wa[c] - Wc[c];
         }
-        hweno_cell_diff<1>(sy, A.pk, ce, Ub, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
+        if constexpr (IFACE)
+          hweno_cell_diff_iface<1>(sy, A.pk, ce, Ua, Ub, Uc, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
+        else
+          hweno_cell_diff<1>(sy, A.pk, ce, Ub, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
       }
       T gt[NC], tt[NC], gb[NC], tb[NC];
       const auto qt = sy.prim(uT);
@@ -640,13 +708,18 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
       const int s3 = slot, s2 = slot == 2 ? 0 : slot + 1, s1 = slot == 0 ? 2 : slot - 1;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        const T g3 = ring[s3][0][c][lane], g2 = ring[s2][0][c][lane], g1 = ring[s1][0][c][lane];
         const T t3 = ring[s3][1][c][lane];
         const T x3 = ring[s3][2][c][lane], x2 = ring[s2][2][c][lane], x1 = ring[s1][2][c][lane];
-        T Dg, Dt;
-        central_corr_k(g3, g2, g1, gc[c], t3, tc[c], Dg, Dt);
-        Gn[c] = fma(T(0.5), topr[0][c][lane] + pG[c], Dg);
-        Tn[c] = fma(T(0.5), topr[1][c][lane] + pT[c], Dt);
+        const T sG = topr[0][c][lane] + pG[c], sT = topr[1][c][lane] + pT[c];
+        const T g2 = ring[s2][0][c][lane], g1 = ring[s1][0][c][lane];
+        if constexpr (kFluxScaled<T>) {
+          const T d0 = gc[c] - prev_row(2, c);
+          interface_flux(g2, g1, d0, t3, tc[c], sG, sT, Gn[c], Tn[c]);
+          prev_row(2, c) = gc[c];
+          gc[c] = d0;
+        } else {
+          interface_flux_plain(ring[s3][0][c][lane], g2, g1, gc[c], t3, tc[c], sG, sT, Gn[c], Tn[c]);
+        }
         Xn[c] = fma(T(7), x2 + x1, -(x3 + xc[c]));
       }
     }
@@ -665,9 +738,9 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
     T Unew[NC], Vnew[NC], Wnew[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      Unew[c] = (T)fma(wl, (double)fprev[0][c][lane] - (double)Gn[c], pend[0][c][lane]);
-      Vnew[c] = (T)fma(wlv, (double)fprev[2][c][lane] - (double)Xn[c], pend[1][c][lane]);
-      Wnew[c] = (T)fma(wlw, (double)fprev[1][c][lane] - (double)Tn[c], pend[2][c][lane]);
+      Unew[c] = (T)fma(wyu, (double)fprev[0][c][lane] - (double)Gn[c], pend[0][c][lane]);
+      Vnew[c] = (T)fma(wyv, (double)fprev[2][c][lane] - (double)Xn[c], pend[1][c][lane]);
+      Wnew[c] = (T)fma(wyw, (double)fprev[1][c][lane] - (double)Tn[c], pend[2][c][lane]);
       fprev[0][c][lane] = Gn[c];
       fprev[1][c][lane] = Tn[c];
       fprev[2][c][lane] = Xn[c];
@@ -700,28 +773,29 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
         const unsigned row = (unsigned)((r - 1) * A.nx + col);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          double lu = RU[c], lv = RV[c], lw = RW[c];
-          if constexpr (SOURCE) {
-            // S(X) = g (0, 0, X_0, X_2) for X = u, v, w of the stage state
-            // (v, w held times dx, dy)
-            if (c >= 2) {
-              const int k = c == 2 ? 0 : 2;
-              lu = fma(A.gravity, (double)Ub[k], lu);
-              lv = fma(A.gravity * s.idx, (double)Vb[k], lv);
-              lw = fma(A.gravity * s.idy, (double)Wb[k], lw);
-            }
-          }
           const double ub = MODE >= kStage2 ? (double)Bu[c] : 0.0;
           const double vb = MODE >= kStage2 ? (double)Bv[c] : 0.0;
           const double wb = MODE >= kStage2 ? (double)Bw[c] : 0.0;
-          const double vtc = (double)vt[c] * s.idx, wtc = (double)wt[c] * s.idy;
-          pend[0][c][lane] = rk_part<MODE>((double)Ub[c], ub, dt, lu);
-          pend[1][c][lane] = rk_part<MODE>(vtc, vb, dt, lv);
-          pend[2][c][lane] = rk_part<MODE>(wtc, wb, dt, lw);
+          double pu = fma(wxu, RU[c], rk_base<MODE>((double)Ub[c], rk_x<MODE>(1.0), ub));
+          double pv = fma(wxv, RV[c], rk_base<MODE>((double)vt[c], wvt, vb));
+          double pw = fma(wxw, RW[c], rk_base<MODE>((double)wt[c], wwt, wb));
+          if constexpr (SOURCE) {
+            // S(X) = g (0, 0, X_0, X_2) for X = u, v, w of the stage state
+            if (c >= 2) {
+              const int k = c == 2 ? 0 : 2;
+              const double g = wl * A.gravity;
+              pu = fma(g, (double)Ub[k], pu);
+              pv = fma(g * A.fk.ilx, (double)Vb[k], pv);
+              pw = fma(g * A.fk.ily, (double)Wb[k], pw);
+            }
+          }
+          pend[0][c][lane] = pu;
+          pend[1][c][lane] = pv;
+          pend[2][c][lane] = pw;
           if (MODE == kStage1 || MODE == kRhs) {
             const unsigned idx = (unsigned)(c * A.plane) + row;
-            st32(A.Vt, idx, (T)vtc);
-            st32(A.Wt, idx, (T)wtc);
+            st32(A.Vt, idx, (T)((double)vt[c] * A.fk.vtx));
+            st32(A.Wt, idx, (T)((double)wt[c] * A.fk.vty));
           }
         }
       }
@@ -729,8 +803,8 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
     // rotate the registers
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      Ua[c] = Ub[c]; Ub[c] = Uc[c];
-      Wa[c] = Wb[c]; Wb[c] = Wc[c];
+      Ub[c] = Uc[c];
+      Wb[c] = Wc[c];
       Vb[c] = Vc[c];
       if (MODE >= kStage2) { Bu[c] = Bun[c]; Bv[c] = Bvn[c]; Bw[c] = Bwn[c]; }
     }
@@ -1811,7 +1885,23 @@ StageArgs<T> base_args(const hweno_problem* p) {
   A.tc = 0.0;
   A.ctl.dim = p->dim;
   A.s = make_scheme(p);
-  A.pk = point_k(A.s);
+  const double lam = Carried<T>::lam;
+  const double vt = point_vt_scale<T>(A.s);
+  A.pk = point_k(A.s, lam, vt);
+  const double F = kFluxScaled<T> ? -19.0 / (960.0 * lam) : 1.0;
+  const double H = kFluxScaled<T> ? 37.0 / (864.0 * lam) : 1.0;
+  FluxK& k = A.fk;
+  k.lx = lam * A.s.dx;
+  k.ly = lam * A.s.dy;
+  k.ilx = A.s.idx / lam;
+  k.ily = A.s.idy / lam;
+  k.vtx = vt * A.s.idx;
+  k.vty = vt * A.s.idy;
+  k.xu = F * A.s.idx;
+  k.yu = F * A.s.idy;
+  k.xv = H * A.s.idx * A.s.idx;
+  k.yw = H * A.s.idy * A.s.idy;
+  k.xw = k.yv = A.s.idx * A.s.idy / (12.0 * lam);
   return A;
 }
 
