@@ -38,19 +38,36 @@ struct SplitRule {
   double state[2][4];
 };
 
-// Workspace scalars of a time step. The alpha accumulators hold the
-// non-negative doubles' bit patterns (atomic max): acc[0..1] the stage-2
-// alphas (written by stage 1), acc[2..3] the stage-3 alphas (by stage 2),
-// acc[4..5] the next stage-1 alphas, i.e. those of the step's result (by
-// stage 3, or by the seeding pass before a run's first step).
+// Workspace scalars of a time step.
 struct StepScalars {
-  unsigned long long acc[6];
   double dt;
   double t0;                      // the step's start time
   double tnew;                    // its end time (t0 + dt, or t_end when clipped)
   int active;
   unsigned flags;
 };
+
+// Accumulators of the Lax-Friedrichs alphas, behind the scalars: kSlots slots,
+// in each one (x, y) pair per set, holding the non-negative doubles' bit
+// patterns (atomic max). A stage's blocks spread over the slots, the next stage
+// takes the maximum over them: a thousand blocks' atomics on one pair of
+// addresses serialise (512^2 FP64: 50 us a stage with one slot, 34 with 32; 33
+// without the atomics). Up to kOneSlotBlocks blocks use one slot, which costs
+// the next stage no reduction (0.5 us a launch: 1D, N = 2000, 34 blocks).
+// Sets: kSet2 the stage-2 alphas (written by stage 1), kSet3 the stage-3 alphas
+// (by stage 2), kSetNext the next step's stage-1 alphas, i.e. those of the
+// step's result (by stage 3), kSetSeed the stage-1 alphas of a call's first step
+// (by the pass over its initial state). Between calls kSet2 and kSetSeed are
+// zero.
+constexpr int kSlots = 32, kSets = 4, kOneSlotBlocks = 64;
+enum AlphaSet { kSet2 = 0, kSet3 = 1, kSetNext = 2, kSetSeed = 3 };
+constexpr size_t kSlotOffset = 2048;   // from the scalars, in bytes
+struct AlphaSlots {
+  unsigned long long v[kSlots][kSets][2];
+};
+__host__ __device__ inline AlphaSlots* alpha_slots(StepScalars* sc) {
+  return (AlphaSlots*)((char*)sc + kSlotOffset);
+}
 
 // Time-step control of a stage-1 launch that computes dt itself (flux-LF): from
 // its alphas by `rule` (production cfl / (ax/hx + ay/hy) with hx, hy = dx, dy;
@@ -80,11 +97,11 @@ struct StageArgs {
   const T* Ub; const T* Vb; const T* Wb;  // RK base B^n = (U^n, V~^n, W~^n), stages 2-3
   T* Uo; T* Vo; T* Wo;                    // new state (stages) or L^1..L^3 (rhs)
   T* Vt; T* Wt;                           // stage 1: V~^n, W~^n; rhs: modified derivatives
-  const double* alpha;                    // [2] LF alphas of this stage
+  const double* alpha;                    // [2] LF alphas of this stage, or null: set alpha_set
+  int alpha_set, next_set;                // of ctl.sc: read from, written to (next_set -1: no)
+  int nslots;                             // accumulator slots in use: 1 or kSlots
   const double* dt;                       // stages 2-3, frozen steps: time step
   const int* active;                      // stages 2-3: 0 = the step is skipped
-  unsigned long long* alpha_next;         // [2] atomic max of the new state's speeds, or null
-  unsigned* flags;                        // sticky state flags, or null
   double* alpha_rec;                      // [2] record of the alphas used, or null
   int nx, ny, rows;                       // rows: output rows per block (2D)
   int plane;                              // nx * ny
@@ -101,23 +118,89 @@ struct StageArgs {
   FluxK fk;
 };
 
-// Start of a stage launch: the stage's dt and time, and whether the step is
-// active. A stage 1 with time-step control computes dt itself from its alphas
-// (every block alike); its first lane also publishes dt, the step's times and
-// the record of the alphas, and clears the stage-3 accumulators. Stage 2 of
-// such a step advances the caller's time and clears the next-step
-// accumulators (read by stage 1, written again by stage 3); stage 3 clears
-// the stage-2 accumulators. Each clear comes after the last read of those
-// accumulators and before their next writer, one kernel boundary apart.
+// Maximum over the wavefront's lanes of a non-negative double, in scalar
+// registers: DPP row shifts, then the row broadcasts (absent lanes give 0).
+template <int CTRL>
+__device__ __forceinline__ double dpp_max_step(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return fmax(v, __hiloint2double(hi, lo));
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = dpp_max_step<0x111>(v);   // row_shr:1, 2, 4, 8
+  v = dpp_max_step<0x112>(v);
+  v = dpp_max_step<0x114>(v);
+  v = dpp_max_step<0x118>(v);
+  v = dpp_max_step<0x142>(v);   // row_bcast:15, 31
+  v = dpp_max_step<0x143>(v);
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), kWave - 1),
+                          __builtin_amdgcn_readlane(__double2loint(v), kWave - 1));
+}
+__device__ __forceinline__ unsigned wave_or(unsigned v) {
+  unsigned r = 0;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) r |= __ballot((v >> b) & 1u) ? 1u << b : 0u;
+  return r;
+}
+// Atomic max of non-negative doubles through their bit patterns (ordered
+// like unsigned integers); order-independent, hence deterministic.
+__device__ __forceinline__ void atomic_max_pos(unsigned long long* p, double v) {
+  atomicMax(p, (unsigned long long)__double_as_longlong(v));
+}
+// One lane adds its block's maxima and state flags to the accumulators.
+template <int DIM>
+__device__ __forceinline__ void raise_alphas(StepScalars* sc, int nslots, int set, int block, double ax,
+                                             double ay, unsigned flag) {
+  unsigned long long* p = alpha_slots(sc)->v[nslots == 1 ? 0 : block % kSlots][set];
+  atomic_max_pos(p, ax);
+  if (DIM == 2) atomic_max_pos(p + 1, ay);
+  if (flag) atomicOr(&sc->flags, flag);
+}
+
+// Start of a stage launch, by every wavefront: the stage's alphas, dt and time,
+// and whether the step is active. A stage 1 with time-step control computes dt
+// itself from its alphas (every block alike); the first wavefront of the first
+// block (`leader`) also publishes dt, the step's times and the record of the
+// alphas, and clears the stage-3 accumulators. Stage 2 of such a step advances
+// the caller's time and clears the next-step and seed accumulators (read by
+// stage 1; the former written again by stage 3); stage 3 clears the stage-2
+// accumulators. Each clear comes after the last read of those accumulators and
+// before their next writer, one kernel boundary apart. A skipped step leaves
+// all but the seed set as they are.
 template <int MODE, typename T>
-__device__ __forceinline__ bool stage_begin(const StageArgs<T>& A, bool leader, double& dt,
-                                            double& tstage) {
+__device__ __forceinline__ bool stage_begin(const StageArgs<T>& A, bool leader, double& ax, double& ay,
+                                            double& dt, double& tstage) {
   dt = 0.0;
   tstage = 0.0;
-  if (MODE == kRhs) return true;
   const StepCtl& c = A.ctl;
+  const int lane = threadIdx.x & (kWave - 1);
+  const bool first = leader && lane == 0;
+  auto clear = [&](int set) {
+    if (lane < kSlots) {
+      unsigned long long* p = alpha_slots(c.sc)->v[lane][set];
+      p[0] = p[1] = 0ull;
+    }
+  };
+  if (A.alpha) {
+    ax = A.alpha[0];
+    ay = A.alpha[1];
+  } else if (A.nslots == 1) {
+    const unsigned long long* p = alpha_slots(c.sc)->v[0][A.alpha_set];
+    ax = __longlong_as_double((long long)p[0]);
+    ay = __longlong_as_double((long long)p[1]);
+  } else {
+    double x = 0.0, y = 0.0;
+    if (lane < kSlots) {
+      const unsigned long long* p = alpha_slots(c.sc)->v[lane][A.alpha_set];
+      x = __longlong_as_double((long long)p[0]);
+      y = __longlong_as_double((long long)p[1]);
+    }
+    ax = wave_max(x);
+    ay = wave_max(y);
+  }
+  if (MODE == kRhs) return true;
   if (MODE == kStage1 && c.sc) {
-    const double ax = A.alpha[0], ay = c.dim == 2 ? A.alpha[1] : 0.0;
+    if (c.dim == 1) ay = 0.0;
     double d = c.rule == HWENO_DT_FIXED ? c.dt_fixed
                                         : c.cfl / (c.dim == 2 ? ax / c.hx + ay / c.hy : ax / c.hx);
     const double t0 = *c.t;
@@ -130,12 +213,18 @@ __device__ __forceinline__ bool stage_begin(const StageArgs<T>& A, bool leader, 
       d = c.t_end - t0;
       tn = c.t_end;
     }
-    if (leader) {
+    if (leader) clear(kSet3);
+    if (leader && !active && A.alpha_set == kSetSeed && lane < kSlots) {
+      // nothing was stepped: the seed stays the next step's alphas
+      AlphaSlots* a = alpha_slots(c.sc);
+      a->v[lane][kSetNext][0] = a->v[lane][kSetSeed][0];
+      a->v[lane][kSetNext][1] = a->v[lane][kSetSeed][1];
+    }
+    if (first) {
       c.sc->dt = d;
       c.sc->t0 = t0;
       c.sc->tnew = tn;
       c.sc->active = active ? 1 : 0;
-      c.sc->acc[2] = c.sc->acc[3] = 0ull;
       if (c.dt_used) *c.dt_used = d;
       if (A.alpha_rec) {
         A.alpha_rec[0] = ax;
@@ -146,19 +235,20 @@ __device__ __forceinline__ bool stage_begin(const StageArgs<T>& A, bool leader, 
     tstage = t0;
     return active;
   }
+  if (MODE == kStage2 && c.sc && leader) clear(kSetSeed);
   if (A.active && *A.active == 0) return false;
   dt = *A.dt;
   tstage = A.t0 ? *A.t0 + A.tc * dt : 0.0;
-  if (leader) {
+  if (first) {
     if (A.alpha_rec) {
-      A.alpha_rec[0] = A.alpha[0];
-      A.alpha_rec[1] = A.ctl.dim == 1 ? 0.0 : A.alpha[1];
+      A.alpha_rec[0] = ax;
+      A.alpha_rec[1] = A.ctl.dim == 1 ? 0.0 : ay;
     }
-    if (c.sc && MODE == kStage2) {
-      *c.t = c.sc->tnew;
-      c.sc->acc[4] = c.sc->acc[5] = 0ull;
-    }
-    if (c.sc && MODE == kStage3) c.sc->acc[0] = c.sc->acc[1] = 0ull;
+    if (c.sc && MODE == kStage2) *c.t = c.sc->tnew;
+  }
+  if (leader && c.sc) {
+    if (MODE == kStage2) clear(kSetNext);
+    if (MODE == kStage3) clear(kSet2);
   }
   return true;
 }
@@ -199,22 +289,6 @@ __device__ __forceinline__ void row_to_lds(const T* base, unsigned row_off, int 
 // own wait insertion does not order every LDS read after a pending copy)
 __device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ unsigned wave_or(unsigned v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o);
-  return v;
-}
-// Atomic max of non-negative doubles through their bit patterns (ordered
-// like unsigned integers); order-independent, hence deterministic.
-__device__ __forceinline__ void atomic_max_pos(unsigned long long* p, double v) {
-  atomicMax(p, (unsigned long long)__double_as_longlong(v));
-}
 
 // ------------------------------------------------------ x-direction sweep
 // The numerical fluxes (flux-1d), (flux-LF) with the central correction
@@ -382,12 +456,11 @@ template <class Sys, typename T, int MODE, bool IFACE>
 __global__ __launch_bounds__(64) void stage1d_kernel(StageArgs<T> A, Sys sy) {
   constexpr int NC = Sys::NC;
   const int lane = threadIdx.x;
-  double dt, tstage;
-  if (!stage_begin<MODE>(A, blockIdx.x == 0 && lane == 0, dt, tstage)) return;
+  double ax, ay, dt, tstage;
+  if (!stage_begin<MODE>(A, blockIdx.x == 0, ax, ay, dt, tstage)) return;
   const int col = blockIdx.x * kXOut - kHalo + lane;
   const int g = map_index(col, A.nx, A.bc[0], A.bc[1]);
   const bool out = lane >= kHalo && lane < kWave - kHalo && col < A.nx;
-  const double ax = A.alpha[0];
   T U[NC], V[NC], W[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
@@ -429,18 +502,15 @@ __global__ __launch_bounds__(64) void stage1d_kernel(StageArgs<T> A, Sys sy) {
       A.Vo[o] = (T)fma(wv, RV[c], rk_base<MODE>((double)vt[c], rk_x<MODE>(A.fk.vtx), vb));
       if (MODE == kStage1 || MODE == kRhs) A.Vt[o] = (T)((double)vt[c] * A.fk.vtx);
     }
-    if (A.alpha_next) {
+    if (A.next_set >= 0) {
       double sy_;
       flag = sy.speeds(Un, smax, sy_);
     }
   }
-  if (A.alpha_next) {
+  if (A.next_set >= 0) {
     smax = wave_max(smax);
     flag = wave_or(flag);
-    if (lane == 0) {
-      atomic_max_pos(A.alpha_next, smax);
-      if (flag && A.flags) atomicOr(A.flags, flag);
-    }
+    if (lane == 0) raise_alphas<1>(A.ctl.sc, A.nslots, A.next_set, blockIdx.x, smax, 0.0, flag);
   }
 }
 
@@ -556,10 +626,10 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
   constexpr int NC = Sys::NC;
   const Scheme& s = A.s;
   const int lane = threadIdx.x;
-  double dt, tstage;
+  double ax, ay, dt, tstage;
   int bx, by;
   xcd_tile(bx, by);
-  if (!stage_begin<MODE>(A, bx == 0 && by == 0 && lane == 0, dt, tstage)) return;
+  if (!stage_begin<MODE>(A, bx == 0 && by == 0, ax, ay, dt, tstage)) return;
   const int col = bx * kXOut - kHalo + lane;
   const int gcol = map_index(col, A.nx, A.bc[0], A.bc[1]);
   const bool out_col = lane >= kHalo && lane < kWave - kHalo && col < A.nx;
@@ -570,7 +640,6 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
   const bool xwall = (special(A.bc[0]) && col0 < 0) || (special(A.bc[1]) && col0 + kWave > A.nx);
   const int y0 = by * A.rows;
   const int y1 = min(y0 + A.rows, A.ny);
-  const double ax = A.alpha[0], ay = A.alpha[1];
   const T a_y = T(ay);
   // weights of the flux differences (F_{i-1/2} - F_{i+1/2}) of the three
   // equations in the new state, along x and y, and of the modified derivatives
@@ -754,7 +823,7 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
         st32(A.Vo, idx, Vnew[c]);
         st32(A.Wo, idx, Wnew[c]);
       }
-      if (A.alpha_next) {
+      if (A.next_set >= 0) {
         double sx_, sy_;
         flag |= sy.speeds(Unew, sx_, sy_);
         smx = fmax(smx, sx_);
@@ -810,24 +879,23 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
     }
     slot = slot == 2 ? 0 : slot + 1;
   }
-  if (A.alpha_next) {
+  if (A.next_set >= 0) {
     smx = wave_max(smx);
     smy = wave_max(smy);
     flag = wave_or(flag);
-    if (lane == 0) {
-      atomic_max_pos(A.alpha_next, smx);
-      atomic_max_pos(A.alpha_next + 1, smy);
-      if (flag && A.flags) atomicOr(A.flags, flag);
-    }
+    if (lane == 0)
+      raise_alphas<2>(A.ctl.sc, A.nslots, A.next_set, blockIdx.x + gridDim.x * blockIdx.y, smx, smy, flag);
   }
 }
 
 // -------------------------------------------- wave-speed reduction (flux-LF)
-// Per-block maxima of the spectral radius over interior cells, in x and y;
+// Per-block maxima of the spectral radius over interior cells, in x and y, to
+// `partial`, or (null) into the accumulators kSetSeed of a run's first step;
 // also raises the state flags.
 template <class Sys, typename T, int DIM>
 __global__ __launch_bounds__(256) void speed_partial_kernel(const T* U, int plane, Sys sy,
-                                                            double* partial, unsigned* flags) {
+                                                            double* partial, StepScalars* sc,
+                                                            int nslots) {
   constexpr int NC = Sys::NC;
   double mx = 0.0, my = 0.0;
   unsigned flag = 0;
@@ -851,9 +919,13 @@ __global__ __launch_bounds__(256) void speed_partial_kernel(const T* U, int plan
   if (threadIdx.x == 0) {
     const int nw = blockDim.x / kWave;
     for (int k = 1; k < nw; ++k) { mx = fmax(mx, sx[k]); my = fmax(my, sy_[k]); flag |= sf[k]; }
-    partial[2 * blockIdx.x] = mx;
-    partial[2 * blockIdx.x + 1] = my;
-    if (flag && flags) atomicOr(flags, flag);
+    if (partial) {
+      partial[2 * blockIdx.x] = mx;
+      partial[2 * blockIdx.x + 1] = my;
+      if (flag) atomicOr(&sc->flags, flag);
+    } else {
+      raise_alphas<DIM>(sc, nslots, kSetSeed, blockIdx.x, mx, my, flag);
+    }
   }
 }
 
@@ -884,21 +956,11 @@ __global__ __launch_bounds__(256) void alpha_out_kernel(const double* partial, i
   if (threadIdx.x == 0) { alpha[0] = ax; alpha[1] = ay; }
 }
 
-// Seeds a run of steps (flux-LF): reduces the per-block maxima of the state's
-// spectral radii into the next-step accumulators (the stage-1 alphas of the
-// first step) and clears the stage-2 and stage-3 accumulators.
-__global__ __launch_bounds__(256) void alpha_seed_kernel(const double* partial, int n,
-                                                         StepScalars* sc) {
-  double ax, ay;
-  reduce_partials(partial, n, &ax, &ay);
-  if (threadIdx.x != 0) return;
-  sc->acc[4] = (unsigned long long)__double_as_longlong(ax);
-  sc->acc[5] = (unsigned long long)__double_as_longlong(ay);
-  for (int k = 0; k < 4; ++k) sc->acc[k] = 0ull;
-}
-
-__global__ void ws_init_kernel(StepScalars* sc) {
-  for (int k = 0; k < 6; ++k) sc->acc[k] = 0ull;
+__global__ __launch_bounds__(kWave) void ws_init_kernel(StepScalars* sc) {
+  const int lane = threadIdx.x;
+  if (lane < kSlots)
+    for (int k = 0; k < kSets; ++k) alpha_slots(sc)->v[lane][k][0] = alpha_slots(sc)->v[lane][k][1] = 0ull;
+  if (lane != 0) return;
   sc->dt = sc->t0 = sc->tnew = 0.0;
   sc->active = 0;
   sc->flags = 0u;
@@ -1515,7 +1577,8 @@ using namespace hweno;
 
 namespace {
 
-constexpr size_t kScalarBytes = 4096;
+constexpr size_t kScalarBytes = 4096;      // StepScalars and AlphaSlots
+static_assert(sizeof(StepScalars) <= kSlotOffset && kSlotOffset + sizeof(AlphaSlots) <= kScalarBytes);
 constexpr int kPartialBlocks = 1024;
 constexpr size_t kPartialBytes = kPartialBlocks * 2 * sizeof(double);
 constexpr int kRowsPerBlock = 32;
@@ -1884,6 +1947,7 @@ StageArgs<T> base_args(const hweno_problem* p) {
   A.t0 = nullptr;
   A.tc = 0.0;
   A.ctl.dim = p->dim;
+  A.next_set = -1;
   A.s = make_scheme(p);
   const double lam = Carried<T>::lam;
   const double vt = point_vt_scale<T>(A.s);
@@ -1912,10 +1976,10 @@ int partial_blocks(size_t plane) {
 
 template <class Sys, typename T, int DIM>
 hweno_status launch_speed_partial(const hweno_problem* p, const T* U, const Sys& sy, double* partial,
-                                  unsigned* flags, hipStream_t st, int* nb) {
+                                  StepScalars* sc, int nslots, hipStream_t st, int* nb) {
   const size_t plane = (size_t)p->nx * p->ny;
   *nb = partial_blocks(plane);
-  speed_partial_kernel<Sys, T, DIM><<<*nb, 256, 0, st>>>(U, (int)plane, sy, partial, flags);
+  speed_partial_kernel<Sys, T, DIM><<<*nb, 256, 0, st>>>(U, (int)plane, sy, partial, sc, nslots);
   return check_launch();
 }
 
@@ -2091,8 +2155,8 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
 }
 
 // Time-stepping loop of hweno_step(s) ((fully-hweno), (2Dfully-hweno)): one
-// seeding pass (per-block maxima of the spectral radii of the initial state,
-// reduced into the stage-1 alphas), then three stage launches per step. Stage 1 computes the
+// seeding pass (the maxima of the spectral radii of the initial state, into the
+// accumulators of the stage-1 alphas), then three stage launches per step. Stage 1 computes the
 // step's dt from its alphas, stage 3 reduces the next step's stage-1 alphas
 // in its epilogue, so steady-state steps launch the three stage kernels only.
 hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_t nsteps,
@@ -2121,16 +2185,17 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
     T* Vt = (T*)wl.base;
     T* Wt = DIM == 2 ? Vt + (size_t)g.nc * P : nullptr;
     auto F = [&](char* b, int f) { return (T*)(b + (size_t)f * g.nc * P * sizeof(T)); };
+    // (a 1D stage has a block per kXOut cells; in 2D a small grid has more)
+    const int nslots = DIM == 1 && (p->nx + kXOut - 1) / kXOut <= kOneSlotBlocks ? 1 : kSlots;
     int nb;
-    hweno_status s2 = launch_speed_partial<Sys, T, DIM>(p, (const T*)u, sy, wl.partial,
-                                                        &wl.sc->flags, stream, &nb);
+    hweno_status s2 =
+        launch_speed_partial<Sys, T, DIM>(p, (const T*)u, sy, nullptr, wl.sc, nslots, stream, &nb);
     if (s2 != HWENO_OK) return s2;
-    alpha_seed_kernel<<<1, 256, 0, stream>>>(wl.partial, nb, wl.sc);
-    if ((s2 = check_launch()) != HWENO_OK) return s2;
     StageArgs<T> A = base_args<T>(p);
     A.dt = &wl.sc->dt;
     A.active = &wl.sc->active;
-    A.flags = &wl.sc->flags;
+    A.alpha = nullptr;
+    A.nslots = nslots;
     A.t0 = &wl.sc->t0;            // stage times t0, t0 + dt, t0 + dt/2
     A.ctl.sc = wl.sc;
     A.ctl.t = t;
@@ -2156,8 +2221,8 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
       A.Ub = nullptr; A.Vb = nullptr; A.Wb = nullptr;
       A.Uo = F(x1, 0); A.Vo = F(x1, 1); A.Wo = DIM == 2 ? F(x1, 2) : nullptr;
       A.Vt = Vt; A.Wt = Wt;
-      A.alpha = (const double*)&wl.sc->acc[4];
-      A.alpha_next = &wl.sc->acc[0];
+      A.alpha_set = k == 0 ? kSetSeed : kSetNext;
+      A.next_set = kSet2;
       A.alpha_rec = rec;
       A.tc = 0.0;
       if ((s2 = launch_stage<Sys, T, DIM>(kStage1, A, sy, stream)) != HWENO_OK) return s2;
@@ -2167,8 +2232,8 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
       A.Ub = (const T*)u; A.Vb = Vt; A.Wb = Wt;
       A.Uo = F(x2, 0); A.Vo = F(x2, 1); A.Wo = DIM == 2 ? F(x2, 2) : nullptr;
       A.Vt = nullptr; A.Wt = nullptr;
-      A.alpha = (const double*)&wl.sc->acc[0];
-      A.alpha_next = &wl.sc->acc[2];
+      A.alpha_set = kSet2;
+      A.next_set = kSet3;
       A.alpha_rec = rec ? rec + 2 : nullptr;
       A.tc = 1.0;
       if ((s2 = launch_stage<Sys, T, DIM>(kStage2, A, sy, stream)) != HWENO_OK) return s2;
@@ -2177,8 +2242,8 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
       // are the next step's stage-1 alphas
       A.U = F(x2, 0); A.V = F(x2, 1); A.W = DIM == 2 ? F(x2, 2) : nullptr;
       A.Uo = (T*)u; A.Vo = (T*)v; A.Wo = (T*)w;
-      A.alpha = (const double*)&wl.sc->acc[2];
-      A.alpha_next = &wl.sc->acc[4];
+      A.alpha_set = kSet3;
+      A.next_set = kSetNext;
       A.alpha_rec = rec ? rec + 4 : nullptr;
       A.tc = 0.5;
       if ((s2 = launch_stage<Sys, T, DIM>(kStage3, A, sy, stream)) != HWENO_OK) return s2;
@@ -2219,7 +2284,7 @@ hweno_status hweno_workspace_init(const hweno_problem* p, void* ws, hipStream_t 
   hweno_status st = validate(p);
   if (st != HWENO_OK) return st;
   if (!ws) return HWENO_EINVAL;
-  ws_init_kernel<<<1, 1, 0, stream>>>((StepScalars*)ws);
+  ws_init_kernel<<<1, kWave, 0, stream>>>((StepScalars*)ws);
   return check_launch();
 }
 
@@ -2235,8 +2300,7 @@ hweno_status hweno_max_wavespeed(const hweno_problem* p, const void* u, double* 
     using Sys = decltype(sy);
     constexpr int DIM = decltype(dimc)::value;
     int nb;
-    hweno_status s2 = launch_speed_partial<Sys, T, DIM>(p, (const T*)u, sy, w.partial,
-                                                        &w.sc->flags, stream, &nb);
+    hweno_status s2 = launch_speed_partial<Sys, T, DIM>(p, (const T*)u, sy, w.partial, w.sc, 1, stream, &nb);
     if (s2 != HWENO_OK) return s2;
     alpha_out_kernel<<<1, 256, 0, stream>>>(w.partial, nb, alpha);
     return check_launch();
@@ -2303,8 +2367,8 @@ hweno_status hweno_step_noalloc(const hweno_problem* p, void* u, void* v, void* 
   void* ws = nullptr;
   if ((st = scratch_on_current_device(&ws)) != HWENO_OK) return st;
   // the scratch keeps the previous call's contents: clear the step scalars
-  // (alpha accumulators, flags) with a kernel, before the step's launches
-  ws_init_kernel<<<1, 1, 0, stream>>>((StepScalars*)ws);
+  // (flags, alpha accumulators) with a kernel, before the step's launches
+  ws_init_kernel<<<1, kWave, 0, stream>>>((StepScalars*)ws);
   if ((st = check_launch()) != HWENO_OK) return st;
   return run_steps(p, u, v, w, 1, dt_rule, cfl, dt_fixed, t_end, t, dt_used, alpha_rec, nullptr,
                    ws, stream, nullptr);
@@ -2468,7 +2532,7 @@ hweno_status hweno_health(const hweno_problem* p, void* ws, hipStream_t stream, 
     return HWENO_EDEVICE;
   if (hipStreamSynchronize(stream) != hipSuccess) return HWENO_EDEVICE;
   if (clear) {
-    ws_init_kernel<<<1, 1, 0, stream>>>(sc);
+    ws_init_kernel<<<1, kWave, 0, stream>>>(sc);
     if (check_launch() != HWENO_OK) return HWENO_EDEVICE;
     if (hipStreamSynchronize(stream) != hipSuccess) return HWENO_EDEVICE;
   }
