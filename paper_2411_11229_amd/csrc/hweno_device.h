@@ -106,6 +106,24 @@ HWENO_HD float rsqrt_nr(float x) {
 #endif
 }
 
+// The value x, rounded: in FP64 the compiler must not contract the product that
+// made it into a later FMA. It would do so only where both are in one basic
+// block, and rows that the stage kernels treat outside their loop would differ
+// in the last bit from those inside. No instruction by itself. FP32, where every
+// row goes through the loop, keeps the contractions.
+HWENO_HD double rounded(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+v"(x));
+#endif
+  return x;
+}
+HWENO_HD float rounded(float x) { return x; }
+template <int N, typename T>
+HWENO_HD void round_all(T (&a)[N]) {
+#pragma unroll
+  for (int c = 0; c < N; ++c) a[c] = rounded(a[c]);
+}
+
 // ---------------------------------------------------------------- HWENO-I
 // One HWENO-I application on one scalar line (a conserved component for the
 // scalar laws, a characteristic variable for systems), section 2.1:
@@ -283,12 +301,12 @@ HWENO_HD void hweno_point_diff(T e1_, T e2_, T S_, T D_, const PointK& k, T& dR,
   const double base = fma(k.K, c, k.Ks * S);
   const double om = o0 * fma(3.0 / 14.0 / lam, D, s);
   const double N = fma(k.X, X, o0 * base);
-  dR = (T)(fma(k.m, om, N) * iSg);
-  dL = (T)(fma(-k.m, om, N) * iSg);
+  dR = rounded((T)(fma(k.m, om, N) * iSg));
+  dL = rounded((T)(fma(-k.m, om, N) * iSg));
   double At;
   if constexpr (sizeof(T) == 8) At = fma(k.At, S, c);
   else At = fma(k.At, S, k.Ac * c);
-  vt = (T)(fma(o0, At, k.Xt * X) * iSd);
+  vt = rounded((T)(fma(o0, At, k.Xt * X) * iSd));
 }
 
 // (P'xi) and its mirror through the same differences (linear, so valid in
@@ -658,6 +676,8 @@ struct Euler {
   HWENO_HD CellEig<T> cell_eig(const T (&U)[NC]) const {
     CellEig<T> e;
     e.q = prim(U);
+    e.q.p = rounded(e.q.p);
+    e.q.Ep = U[E_] + e.q.p;
     const T c2 = T(gas) * e.q.p * e.q.ir;
     const T ic = rsqrt_nr(c2);
     e.c = c2 * ic;
@@ -676,16 +696,16 @@ struct Euler {
     const Eig<T> r = roe_eig(UL, UR);
     CellEig<T> e;
     e.q = {};
-    e.q.mu = r.mu;
-    e.q.nu = r.nu;
-    e.q.k = r.k;
-    e.c = r.c;
-    e.H = r.H;
-    e.b1h = T(0.5) * r.b1;
-    e.b2h = T(0.5) * r.b2;
+    e.q.mu = rounded(r.mu);
+    e.q.nu = rounded(r.nu);
+    e.q.k = rounded(r.k);
+    e.c = rounded(r.c);
+    e.H = rounded(r.H);
+    e.b1h = rounded(T(0.5) * r.b1);
+    e.b2h = rounded(T(0.5) * r.b2);
     e.ich = T(0.5) * r.ic;
-    e.muc = r.mu * r.c;
-    e.nuc = r.nu * r.c;
+    e.muc = e.q.mu * e.c;
+    e.nuc = e.q.nu * e.c;
     return e;
   }
   // w = L x (the same L as project): with s' = s/2 and t' = t/2,
@@ -779,6 +799,17 @@ struct Euler {
     return f;
   }
 };
+
+// prim for the stage kernels, its pressure rounded (see rounded).
+template <class Sys, typename T>
+HWENO_HD auto prim_rounded(const Sys& sy, const T (&U)[Sys::NC]) {
+  auto q = sy.prim(U);
+  if constexpr (Sys::kChar) {
+    q.p = rounded(q.p);
+    q.Ep = U[Sys::NC - 1] + q.p;
+  }
+  return q;
+}
 
 // HWENO-I on one cell for a system, in direction D: project the stencil on
 // the characteristic basis of the cell centre, apply hweno_point to every

@@ -377,20 +377,23 @@ __device__ __forceinline__ void sweep_x(const Sys& sy, const Scheme& s, const Po
     }
   }
   // pointwise f, h' = f'(u) v', eta' = f'(u) w' at the cell centre
-  T f[NC], hf[NC], e[NC];
+  T f[NC], hf[NC], e[NC] = {};
   sy.template flux<0>(U, ce.q, f);
   sy.template jac<0>(U, ce.q, V, hf);
   if constexpr (NF == 3) sy.template jac<0>(U, ce.q, W, e);
+  round_all(f);
+  round_all(hf);
+  round_all(e);
   // Lax-Friedrichs sums of this cell's faces (flux-LF), halved at the
   // interface: f(u^-) + a u^- at x_{i+1/2}, f(u^+) - a u^+ at x_{i-1/2}
   T mF[NC], mH[NC], pF[NC], pH[NC];
   {
     const T a = T(alpha);
     T fr[NC], hr[NC], fl[NC], hl[NC];
-    const auto qr = sy.prim(uR);
+    const auto qr = prim_rounded(sy, uR);
     sy.template flux<0>(uR, qr, fr);
     sy.template jac<0>(uR, qr, vR, hr);
-    const auto ql = sy.prim(uL);
+    const auto ql = prim_rounded(sy, uL);
     sy.template flux<0>(uL, ql, fl);
     sy.template jac<0>(uL, ql, vL, hl);
 #pragma unroll
@@ -592,8 +595,8 @@ __device__ __forceinline__ void finish_row(const StageArgs<T>& A, int r, bool xw
   }
 #pragma unroll
   for (int c = 0; c < Sys::NC; ++c) {
-    V[c] = T(A.fk.lx) * V[c];
-    W[c] = T(A.fk.ly) * W[c];
+    V[c] = rounded(T(A.fk.lx) * V[c]);
+    W[c] = rounded(T(A.fk.ly) * W[c]);
   }
 }
 
@@ -648,8 +651,8 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
   const double wyu = wl * A.fk.yu, wyv = wl * A.fk.yv, wyw = wl * A.fk.yw;
   const double wvt = rk_x<MODE>(A.fk.vtx), wwt = rk_x<MODE>(A.fk.vty);
 
-  // Rows march upwards; at iteration r the rows r-2, r-1 (registers) and r
-  // (just loaded) are present. Iteration r does: the pointwise y-fluxes of
+  // Rows march upwards; at iteration r the rows r-2, r-1 and r (just loaded)
+  // are present. Iteration r does: the pointwise y-fluxes of
   // row r; the HWENO of row r-1 in y, then in x with the same
   // characteristic basis; the y-interface (r-2)+1/2 and with it the output
   // row r-2; the x-sweep of row r-1, whose flux difference and RK
@@ -669,7 +672,11 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
   // pointwise g (FP64: the difference g_k - g_{k-1}), theta, xi of rows k =
   // r-3, r-2, r-1, slot (row mod 3); each lane only touches its own column
   __shared__ T ring[3][3][NC][kWave];
-  int slot = ((y0 - 2) % 3 + 3) % 3;     // slot of row r (and of row r-3)
+  // FP64: rows y0-2 and y0-1 are taken before the loop, which starts at y0
+  // (FP32: at y0-2, which leaves its results as they were, see rounded())
+  constexpr bool kAhead = sizeof(T) == 8;
+  const int r0 = kAhead ? y0 : y0 - 2;
+  int slot = (r0 % 3 + 3) % 3;           // slot of row r (and of row r-3)
   // Lax-Friedrichs sums g(u) + a u, theta + a w at the top face of row r-2
   __shared__ T topr[2][NC][kWave];
   // y-interface fluxes of the u-, w- and v-equation at (r-3)+1/2, scaled as
@@ -682,19 +689,62 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
 
   T Un[NC], Vn[NC], Wn[NC];
   T Bu[NC], Bv[NC], Bw[NC];              // RK base of row r-1 (stages 2-3)
-  // The y-work below runs in every iteration, also in the first ones, whose
-  // results are never used (so that it forms one block of straight-line code
-  // the compiler can schedule across): start from an admissible state.
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    Ub[c] = T(c == 0 ? 1.0 : (c == NC - 1 ? 2.0 : 0.0));
-    Wb[c] = Vb[c] = T(0);
-    prev_row(0, c) = Ub[c];
-    prev_row(1, c) = prev_row(2, c) = T(0);
-  }
   int rule_n;
-  load_row<Sys, WALLS>(A, tstage, y0 - 2, col, gcol, Un, Vn, Wn, rule_n);
-  for (int r = y0 - 2; r < y1 + 2; ++r) {
+  if constexpr (kAhead) {
+    // they enter as stencil rows only: their pointwise y-fluxes, both rows'
+    // loads in flight together. (512^2: 33.1 -> 30.5 us a stage, 60x240 14.6 ->
+    // 11.8, against two iterations of the loop with its unused y-HWENO.)
+    T Up[NC], Vp[NC], Wp[NC];
+    int rule_p;
+    load_row<Sys, WALLS>(A, tstage, y0 - 2, col, gcol, Un, Vn, Wn, rule_n);
+    load_row<Sys, WALLS>(A, tstage, y0 - 1, col, gcol, Up, Vp, Wp, rule_p);
+    finish_row<Sys, WALLS>(A, y0 - 2, xwall, xm, xf, rule_n, Un, Vn, Wn);
+    finish_row<Sys, WALLS>(A, y0 - 1, xwall, xm, xf, rule_p, Up, Vp, Wp);
+    auto pointwise = [&](int sl, const T (&U)[NC], const T (&V)[NC], const T (&W)[NC], T (&g)[NC]) {
+      T th[NC], xi[NC];
+      const auto q = prim_rounded(sy, U);
+      sy.template flux<1>(U, q, g);
+      sy.template jac<1>(U, q, W, th);
+      sy.template jac<1>(U, q, V, xi);
+      round_all(g);
+      round_all(th);
+      round_all(xi);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        ring[sl][0][c][lane] = g[c];
+        ring[sl][1][c][lane] = th[c];
+        ring[sl][2][c][lane] = xi[c];
+      }
+    };
+    const int s2 = slot == 2 ? 0 : slot + 1, s1 = slot == 0 ? 2 : slot - 1;
+    T g2[NC], g1[NC];
+    pointwise(s2, Un, Vn, Wn, g2);
+    pointwise(s1, Up, Vp, Wp, g1);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      prev_row(0, c) = Un[c];
+      prev_row(1, c) = Wn[c];
+      ring[s1][0][c][lane] = g1[c] - g2[c];
+      prev_row(2, c) = g1[c];
+      Ub[c] = Up[c];
+      Vb[c] = Vp[c];
+      Wb[c] = Wp[c];
+    }
+  } else {
+    // start from an admissible state
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      Ub[c] = T(c == 0 ? 1.0 : (c == NC - 1 ? 2.0 : 0.0));
+      Wb[c] = Vb[c] = T(0);
+      prev_row(0, c) = Ub[c];
+      prev_row(1, c) = prev_row(2, c) = T(0);
+    }
+  }
+  load_row<Sys, WALLS>(A, tstage, r0, col, gcol, Un, Vn, Wn, rule_n);
+  // The y-work below runs in every iteration, also in the first ones, whose
+  // interface and output row are never used (so that it forms one block of
+  // straight-line code the compiler can schedule across).
+  for (int r = r0; r < y1 + 2; ++r) {
     T Uc[NC], Vc[NC], Wc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) { Uc[c] = Un[c]; Vc[c] = Vn[c]; Wc[c] = Wn[c]; }
@@ -716,10 +766,13 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
     // pointwise g, theta = g'(u) w, xi = g'(u) v of row r
     T gc[NC], tc[NC], xc[NC];
     {
-      const auto q = sy.prim(Uc);
+      const auto q = prim_rounded(sy, Uc);
       sy.template flux<1>(Uc, q, gc);
       sy.template jac<1>(Uc, q, Wc, tc);
       sy.template jac<1>(Uc, q, Vc, xc);
+      round_all(gc);
+      round_all(tc);
+      round_all(xc);
     }
     // HWENO in y of row r-1: u at its top and bottom faces, w~, and the LF
     // sums there
@@ -756,10 +809,10 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
           hweno_cell_diff<1>(sy, A.pk, ce, Ub, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
       }
       T gt[NC], tt[NC], gb[NC], tb[NC];
-      const auto qt = sy.prim(uT);
+      const auto qt = prim_rounded(sy, uT);
       sy.template flux<1>(uT, qt, gt);
       sy.template jac<1>(uT, qt, wT, tt);
-      const auto qb = sy.prim(uB);
+      const auto qb = prim_rounded(sy, uB);
       sy.template flux<1>(uB, qb, gb);
       sy.template jac<1>(uB, qb, wB, tb);
 #pragma unroll
