@@ -108,9 +108,9 @@ HWENO_HD float rsqrt_nr(float x) {
 
 // The value x, rounded: in FP64 the compiler must not contract the product that
 // made it into a later FMA. It would do so only where both are in one basic
-// block, and rows that the stage kernels treat outside their loop would differ
-// in the last bit from those inside. No instruction by itself. FP32, where every
-// row goes through the loop, keeps the contractions.
+// block, and a row's last bits would depend on where a stage kernel treats it
+// (in its loop, before it, or in the tile kernel). No instruction by itself.
+// FP32, where every row goes through the marcher's loop, keeps the contractions.
 HWENO_HD double rounded(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm("" : "+v"(x));

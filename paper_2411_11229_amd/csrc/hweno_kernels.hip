@@ -941,6 +941,226 @@ __global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
   }
 }
 
+// Shared-memory barrier of a block: orders LDS accesses only.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The same stage for short strips ("tile"): one wavefront per row. A block of
+// H + 2 wavefronts takes H output rows of 60 columns; wavefront w does row
+// q = y0 - 1 + w: the y-HWENO and the pointwise y-fluxes of its row go to LDS,
+// then, in the H inner wavefronts, the x-sweep; after one barrier each of them
+// forms the two y-interfaces of its row from LDS and stores it. The marcher's
+// warm-up (two rows of y-work on each side of every strip, one after the other
+// in one wavefront) becomes two wavefronts beside the others, so that a strip
+// of a few rows takes the time of one row instead of H + 4. The arithmetic of
+// every row is the marcher's, so the results are the same bit for bit. It is
+// bound by latency: the start, one row's loads (2.6 us) and a row's serial
+// arithmetic (3.5 us). FP64 only (in FP32 a row's bits depend on the loop it is
+// compiled into, see rounded()). Measured times at the rule (tile_rows).
+constexpr int kTileRows = 6;                       // most output rows of a block
+constexpr int kTileThreads = (kTileRows + 2) * kWave;
+// LDS of a block: per row y0-2 .. y0+H+1 the pointwise g, theta, xi; per row
+// y0-1 .. y0+H the LF sums of its top and bottom face for g and theta
+template <int NC, typename T>
+constexpr size_t tile_lds(int H) {
+  return ((size_t)(H + 4) * 3 + (size_t)(H + 2) * 4) * NC * kWave * sizeof(T);
+}
+
+template <class Sys, typename T, int MODE, int VAR>
+__global__ __launch_bounds__(kTileThreads, 2) void stage2d_tile_kernel(StageArgs<T> A, Sys sy) {
+  constexpr bool WALLS = (VAR & kVarWalls) != 0;
+  constexpr bool IFACE = (VAR & kVarIface) != 0;
+  constexpr bool SOURCE = (VAR & kVarSource) != 0 && Sys::kChar && Sys::NC == 4;
+  constexpr int NC = Sys::NC;
+  constexpr int R = NC * kWave;                    // values of one field of one row
+  const Scheme& s = A.s;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  double ax, ay, dt, tstage;
+  int bx, by;
+  xcd_tile(bx, by);
+  if (!stage_begin<MODE>(A, bx == 0 && by == 0 && wv == 0, ax, ay, dt, tstage)) return;
+  const int col0 = bx * kXOut - kHalo;
+  const int col = col0 + lane;
+  const int gcol = map_index(col, A.nx, A.bc[0], A.bc[1]);
+  const bool xm = mirrored(col, A.nx, A.bc[0], A.bc[1]);
+  const int xf = fixed_side(col, A.nx, A.bc[0], A.bc[1]);
+  auto special = [](int b) { return b == kBcReflective || b == kBcDirichlet; };
+  const bool xwall = (special(A.bc[0]) && col0 < 0) || (special(A.bc[1]) && col0 + kWave > A.nx);
+  const int y0 = by * A.rows;
+  const int H = min(A.rows, A.ny - y0);            // output rows of this block
+  const int q = y0 - 1 + wv;
+  const bool run = wv < H + 2;                     // (fewer rows in the last strip)
+  const bool inner = wv >= 1 && wv <= H;
+  const bool out = inner && lane >= kHalo && lane < kWave - kHalo && col < A.nx;
+  extern __shared__ __align__(16) char tile_smem[];
+  T* const rowsF = (T*)tile_smem;                  // row q is slot wv + 1
+  T* const rowsM = rowsF + (A.rows + 4) * 3 * R;   // row q is slot wv: mG, mT, pG, pT
+
+  T Ub[NC], Vb[NC], Wb[NC], wt[NC];
+  typename Sys::template CellEig<T> ce;
+  if (run) {
+    T Ua[NC], Va[NC], Wa[NC], Uc[NC], Vc[NC], Wc[NC];
+    int ra, rb, rc;
+    load_row<Sys, WALLS>(A, tstage, q, col, gcol, Ub, Vb, Wb, rb);
+    load_row<Sys, WALLS>(A, tstage, q - 1, col, gcol, Ua, Va, Wa, ra);
+    load_row<Sys, WALLS>(A, tstage, q + 1, col, gcol, Uc, Vc, Wc, rc);
+    finish_row<Sys, WALLS>(A, q, xwall, xm, xf, rb, Ub, Vb, Wb);
+    finish_row<Sys, WALLS>(A, q - 1, xwall, xm, xf, ra, Ua, Va, Wa);
+    finish_row<Sys, WALLS>(A, q + 1, xwall, xm, xf, rc, Uc, Vc, Wc);
+    // pointwise g, theta = g'(u) w, xi = g'(u) v of a row, to its slot
+    auto pointwise = [&](int slot, const T (&U)[NC], const T (&V)[NC], const T (&W)[NC]) {
+      T g[NC], th[NC], xi[NC];
+      const auto pr = prim_rounded(sy, U);
+      sy.template flux<1>(U, pr, g);
+      sy.template jac<1>(U, pr, W, th);
+      sy.template jac<1>(U, pr, V, xi);
+      round_all(g);
+      round_all(th);
+      round_all(xi);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        rowsF[(slot * 3 + 0) * R + c * kWave + lane] = g[c];
+        rowsF[(slot * 3 + 1) * R + c * kWave + lane] = th[c];
+        rowsF[(slot * 3 + 2) * R + c * kWave + lane] = xi[c];
+      }
+    };
+    pointwise(wv + 1, Ub, Vb, Wb);
+    if (wv == 0) pointwise(0, Ua, Va, Wa);
+    if (wv == H + 1) pointwise(H + 3, Uc, Vc, Wc);
+    // HWENO in y of row q: u at its top and bottom faces, w~, the LF sums there
+    ce = sy.cell_eig(Ub);
+    T uT[NC], uB[NC], wT[NC], wB[NC];
+    if constexpr (IFACE && sizeof(T) == 4) {
+      // mesh width 1 for the scaled derivatives
+      hweno_cell_b<1, true>(sy, s, 1.0, 1.0, ce.q, Ua, Ub, Uc, Wa, Wc, uT, uB, wt);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) face_derivs(Ua[c], Ub[c], Uc[c], Wa[c], Wc[c], T(1), wT[c], wB[c]);
+    } else {
+      T E1[NC], E2[NC], Sw[NC], Dw[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        E1[c] = Ub[c] - Ua[c];
+        E2[c] = Uc[c] - Ub[c];
+        Sw[c] = Wa[c] + Wc[c];
+        Dw[c] = Wa[c] - Wc[c];
+      }
+      if constexpr (IFACE)
+        hweno_cell_diff_iface<1>(sy, A.pk, ce, Ua, Ub, Uc, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
+      else
+        hweno_cell_diff<1>(sy, A.pk, ce, Ub, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
+    }
+    T gt[NC], tt[NC], gb[NC], tb[NC];
+    const T a_y = T(ay);
+    const auto qt = prim_rounded(sy, uT);
+    sy.template flux<1>(uT, qt, gt);
+    sy.template jac<1>(uT, qt, wT, tt);
+    const auto qb = prim_rounded(sy, uB);
+    sy.template flux<1>(uB, qb, gb);
+    sy.template jac<1>(uB, qb, wB, tb);
+    T* m = rowsM + wv * 4 * R + lane;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      m[c * kWave] = fma(a_y, uT[c], gt[c]);
+      m[R + c * kWave] = fma(a_y, wT[c], tt[c]);
+      m[2 * R + c * kWave] = fma(-a_y, uB[c], gb[c]);
+      m[3 * R + c * kWave] = fma(-a_y, wB[c], tb[c]);
+    }
+  }
+  const double wl = rk_wl<MODE>(dt);
+  double PU[NC], PV[NC], PW[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) PU[c] = PV[c] = PW[c] = 0.0;
+  if (inner) {
+    // x-sweep and the RK combination without the y part; the scheduler must
+    // not interleave it with the y-work (both working sets would spill)
+    __builtin_amdgcn_sched_barrier(0);
+    T Bu[NC], Bv[NC], Bw[NC];
+    if constexpr (MODE >= kStage2) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const unsigned idx = (unsigned)(c * A.plane + q * A.nx + gcol);
+        Bu[c] = ld32(A.Ub, idx);
+        Bv[c] = ld32(A.Vb, idx);
+        Bw[c] = ld32(A.Wb, idx);
+      }
+    }
+    double RU[NC], RV[NC], RW[NC];
+    T vt[NC];
+    sweep_x<3, IFACE>(sy, s, A.pk, ax, ce, Ub, Vb, Wb, RU, RV, RW, vt);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const double ub = MODE >= kStage2 ? (double)Bu[c] : 0.0;
+      const double vb = MODE >= kStage2 ? (double)Bv[c] : 0.0;
+      const double wb = MODE >= kStage2 ? (double)Bw[c] : 0.0;
+      PU[c] = fma(wl * A.fk.xu, RU[c], rk_base<MODE>((double)Ub[c], rk_x<MODE>(1.0), ub));
+      PV[c] = fma(wl * A.fk.xv, RV[c], rk_base<MODE>((double)vt[c], rk_x<MODE>(A.fk.vtx), vb));
+      PW[c] = fma(wl * A.fk.xw, RW[c], rk_base<MODE>((double)wt[c], rk_x<MODE>(A.fk.vty), wb));
+      if constexpr (SOURCE) {
+        // S(X) = g (0, 0, X_0, X_2) for X = u, v, w of the stage state
+        if (c >= 2) {
+          const int k = c == 2 ? 0 : 2;
+          const double g = wl * A.gravity;
+          PU[c] = fma(g, (double)Ub[k], PU[c]);
+          PV[c] = fma(g * A.fk.ilx, (double)Vb[k], PV[c]);
+          PW[c] = fma(g * A.fk.ily, (double)Wb[k], PW[c]);
+        }
+      }
+      if (MODE == kStage1 || MODE == kRhs) {
+        const unsigned idx = (unsigned)(c * A.plane + q * A.nx + col);
+        if (out) {
+          st32(A.Vt, idx, (T)((double)vt[c] * A.fk.vtx));
+          st32(A.Wt, idx, (T)((double)wt[c] * A.fk.vty));
+        }
+      }
+    }
+  }
+  lds_barrier();
+  double smx = 0.0, smy = 0.0;
+  unsigned flag = 0;
+  if (out) {
+    // y-interfaces q-1/2 and q+1/2: minus side = top face of the row below,
+    // plus side = bottom face of the row above; central correction from two
+    // rows on either side
+    const double wyu = wl * A.fk.yu, wyv = wl * A.fk.yv, wyw = wl * A.fk.yw;
+    T Un[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      auto F = [&](int j, int f) -> T { return rowsF[((wv + 1 + j) * 3 + f) * R + c * kWave + lane]; };
+      auto M = [&](int j, int f) -> T { return rowsM[((wv + j) * 4 + f) * R + c * kWave + lane]; };
+      T G[2], Tn[2], X[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {                // interface q + k - 1/2
+        const T sG = M(k - 1, 0) + M(k, 2), sT = M(k - 1, 1) + M(k, 3);
+        const T hm = F(k - 2, 1), hp = F(k + 1, 1);
+        const T g0 = F(k - 2, 0), g1 = F(k - 1, 0), g2 = F(k, 0), g3 = F(k + 1, 0);
+        if constexpr (kFluxScaled<T>)
+          interface_flux(g1 - g0, g2 - g1, g3 - g2, hm, hp, sG, sT, G[k], Tn[k]);
+        else
+          interface_flux_plain(g0, g1, g2, g3, hm, hp, sG, sT, G[k], Tn[k]);
+        X[k] = fma(T(7), F(k - 1, 2) + F(k, 2), -(F(k - 2, 2) + F(k + 1, 2)));
+      }
+      const unsigned idx = (unsigned)(c * A.plane + q * A.nx + col);
+      Un[c] = (T)fma(wyu, (double)G[0] - (double)G[1], PU[c]);
+      st32(A.Uo, idx, Un[c]);
+      st32(A.Vo, idx, (T)fma(wyv, (double)X[0] - (double)X[1], PV[c]));
+      st32(A.Wo, idx, (T)fma(wyw, (double)Tn[0] - (double)Tn[1], PW[c]));
+    }
+    if (A.next_set >= 0) flag = sy.speeds(Un, smx, smy);
+  }
+  if (A.next_set >= 0 && inner) {
+    smx = wave_max(smx);
+    smy = wave_max(smy);
+    flag = wave_or(flag);
+    if (lane == 0)
+      raise_alphas<2>(A.ctl.sc, A.nslots, A.next_set, (blockIdx.x + gridDim.x * blockIdx.y) * kTileRows + wv,
+                      smx, smy, flag);
+  }
+}
+
 // -------------------------------------------- wave-speed reduction (flux-LF)
 // Per-block maxima of the spectral radius over interior cells, in x and y, to
 // `partial`, or (null) into the accumulators kSetSeed of a run's first step;
@@ -1905,6 +2125,26 @@ int balanced_rows(long col_blocks, int rows, bool known, int per_cu, int cus, do
   return best;
 }
 
+// Rows of a block of the tile kernel, 0 for the marcher: the fewest with which
+// the blocks are at most one a CU, so that every row of the grid is under way
+// at once. A stage then takes about the time of one row; with more blocks a
+// second round follows (a block's LDS leaves room for one a CU, at one or two
+// rows for two) and the marcher, whose blocks share rows' warm-up over more
+// rows, is as fast. Measured (FP64 Euler, us a stage, marcher | tile): 60x60
+// 11.5 | 7.8, 60x240 11.8 | 8.1, 120x240 12.1 | 8.8, 240x240 14.0 | 10.8;
+// beyond the line 320x256 17.7 | 16.0 at best, 385x250 18.5 | 18.6.
+int tile_rows(long col_blocks, int ny, int cus) {
+  for (int h = 1; h <= kTileRows; ++h)
+    if (col_blocks * ((ny + h - 1) / h) <= cus) return h;
+  return 0;
+}
+
+// The tile kernel of a stage (FP64; nullptr for FP32, which has none).
+template <class Sys, typename T, int MODE, int VAR>
+auto tile_kernel() {
+  if constexpr (sizeof(T) == 8) return stage2d_tile_kernel<Sys, T, MODE, VAR>;
+  else return nullptr;
+}
 
 template <class Sys, typename T, int DIM>
 hweno_status launch_stage(int mode, const StageArgs<T>& A0, const Sys& sy, hipStream_t st) {
@@ -1929,25 +2169,33 @@ hweno_status launch_stage(int mode, const StageArgs<T>& A0, const Sys& sy, hipSt
       modes(std::false_type{});
     }
   } else {
-    auto go = [&](auto kernel, auto tag) {
+    const int col_blocks = (A.nx + kXOut - 1) / kXOut;
+    auto go = [&](auto kernel, auto tile, auto tag) {
       int per_cu = 0, cus = 0;
       const bool known = occupancy<decltype(tag)::value, kWave>(kernel, &per_cu, &cus);
+      const int forced = g_strip_rows.load(std::memory_order_relaxed);
+      if constexpr (sizeof(T) == 8) {
+        A.rows = known && forced <= 0 ? tile_rows(col_blocks, A.ny, cus) : 0;
+        if (A.rows > 0) {
+          const dim3 grid(col_blocks, (A.ny + A.rows - 1) / A.rows);
+          tile<<<grid, (A.rows + 2) * kWave, tile_lds<Sys::NC, T>(A.rows), st>>>(A, sy);
+          return;
+        }
+      }
       // warm-up: two rows of loads and y-pointwise fluxes, two of y-HWENO,
       // about one full row in all
-      const int forced = g_strip_rows.load(std::memory_order_relaxed);
-      A.rows = forced > 0 ? forced
-                          : balanced_rows((A.nx + kXOut - 1) / kXOut, A.ny, known, per_cu, cus, 1.0, 32);
-      dim3 grid((A.nx + kXOut - 1) / kXOut, (A.ny + A.rows - 1) / A.rows);
+      A.rows = forced > 0 ? forced : balanced_rows(col_blocks, A.ny, known, per_cu, cus, 1.0, 32);
+      dim3 grid(col_blocks, (A.ny + A.rows - 1) / A.rows);
       kernel<<<grid, kWave, 0, st>>>(A, sy);
     };
     auto modes = [&](auto var) {
       constexpr int V = decltype(var)::value;
       constexpr int kT = 16 * V;   // separate occupancy cache entries
       switch (mode) {
-        case kRhs: go(stage2d_kernel<Sys, T, kRhs, V>, std::integral_constant<int, kRhs + kT>{}); break;
-        case kStage1: go(stage2d_kernel<Sys, T, kStage1, V>, std::integral_constant<int, kStage1 + kT>{}); break;
-        case kStage2: go(stage2d_kernel<Sys, T, kStage2, V>, std::integral_constant<int, kStage2 + kT>{}); break;
-        default: go(stage2d_kernel<Sys, T, kStage3, V>, std::integral_constant<int, kStage3 + kT>{}); break;
+        case kRhs: go(stage2d_kernel<Sys, T, kRhs, V>, tile_kernel<Sys, T, kRhs, V>(), std::integral_constant<int, kRhs + kT>{}); break;
+        case kStage1: go(stage2d_kernel<Sys, T, kStage1, V>, tile_kernel<Sys, T, kStage1, V>(), std::integral_constant<int, kStage1 + kT>{}); break;
+        case kStage2: go(stage2d_kernel<Sys, T, kStage2, V>, tile_kernel<Sys, T, kStage2, V>(), std::integral_constant<int, kStage2 + kT>{}); break;
+        default: go(stage2d_kernel<Sys, T, kStage3, V>, tile_kernel<Sys, T, kStage3, V>(), std::integral_constant<int, kStage3 + kT>{}); break;
       }
     };
     bool walls = false;

@@ -1,7 +1,9 @@
-"""The 2D forward stage kernels choose how many rows a block takes; no choice
-may change a result. Small grids (last strips of one row, of fewer rows than
-the others, one strip for everything; the last column block ragged, or full)
-with every kind of boundary, the source, both bases and a scalar law: the
+"""The 2D forward stage kernels choose how many rows a block takes, and in
+FP64 whether its rows go through one wavefront or one each; no choice may
+change a result. Small grids (last strips of one row, of fewer rows than the
+others, one strip for everything; the last column block ragged, or full; the
+most rows that a block takes at once, and the first grid beyond) with every
+kind of boundary, the source, both bases and a scalar law: the
 operator and one step, the kernels' own choice against forced strip heights,
 bit for bit (the rows' arithmetic is the same, so no tolerance)."""
 import pytest
@@ -29,13 +31,13 @@ def _workload(kind, nx, ny):
     return WL.euler2d_quadrants(nx, seed=4001, ny=ny), {}
 
 
-CASES = [('quadrants', 61, 37), ('quadrants', 121, 250), ('quadrants', 6, 5), ('interface', 60, 41),
-         ('walls', 59, 23), ('rayleigh-taylor', 40, None), ('double-mach', 34, None),
+CASES = [('quadrants', 61, 37), ('quadrants', 121, 250), ('quadrants', 6, 5),
+         ('quadrants', 300, 301), ('quadrants', 300, 307), ('interface', 60, 41), ('walls', 59, 23), ('rayleigh-taylor', 40, None), ('double-mach', 34, None),
          ('burgers', 70, None)]
 
 
 @pytest.mark.parametrize('precision', ['f64', 'f32'])
-@pytest.mark.parametrize('kind,nx,ny', CASES, ids=[f'{c[0]}-{c[1]}' for c in CASES])
+@pytest.mark.parametrize('kind,nx,ny', CASES, ids=[f'{c[0]}-{c[1]}x{c[2]}' for c in CASES])
 def test_rows_per_block_leave_results_bit_identical(kind, nx, ny, precision):
     w, extra = _workload(kind, nx, ny)
     dtype = torch.float64 if precision == 'f64' else torch.float32
