@@ -23,7 +23,7 @@
 #include <type_traits>
 
 #include "../../include/hweno.h"
-#include "hweno_adjoint.h"
+#include "hweno_adjoint_diff.h"
 #include "hweno_device.h"
 
 namespace hweno {
@@ -266,25 +266,33 @@ template <typename T>
 __device__ __forceinline__ void st32(T* base, unsigned idx, T v) {
   *(T*)((char*)base + idx * (unsigned)sizeof(T)) = v;
 }
-// Asynchronous copy of kWave consecutive elements of one row (from column
+// Asynchronous copies of kWave consecutive elements of a row (from column
 // col0, columns outside [0, nx) clamped to the edge) straight from global memory into
 // LDS (dst[0..kWave)), with no VGPR in between: each 4-byte load of a wave
 // writes lane i's word at byte 4i of its 256-byte part. The caller orders
-// it with LDS reads of dst: wait_copies() before reading the copy,
-// wait_lds_reads() after the last read of dst's previous contents.
+// them with LDS reads of dst: wait_copies() before reading the copy,
+// wait_lds_reads() after the last read of dst's previous contents. The lanes'
+// byte offsets in a row are formed once (one VALU instruction a load is left).
 template <typename T>
-__device__ __forceinline__ void row_to_lds(const T* base, unsigned row_off, int col0, int nx, T* dst,
-                                           int lane) {
-  constexpr int P = sizeof(T) / 4;
+struct RowCopy {
+  static constexpr int P = sizeof(T) / 4;
+  unsigned off[P];
+  __device__ __forceinline__ RowCopy(int col0, int nx, int lane) {
 #pragma unroll
-  for (int j = 0; j < P; ++j) {
-    const int col = max(0, min(col0 + j * (kWave / P) + lane / P, nx - 1));
-    const unsigned byte = (row_off + (unsigned)col) * (unsigned)sizeof(T) + 4u * (unsigned)(lane % P);
-    __builtin_amdgcn_global_load_lds(
-        (const __attribute__((address_space(1))) void*)((const char*)base + byte),
-        (__attribute__((address_space(3))) void*)((char*)dst + 256 * j), 4, 0, 0);
+    for (int j = 0; j < P; ++j) {
+      const int col = max(0, min(col0 + j * (kWave / P) + lane / P, nx - 1));
+      off[j] = (unsigned)col * (unsigned)sizeof(T) + 4u * (unsigned)(lane % P);
+    }
   }
-}
+  __device__ __forceinline__ void operator()(const T* base, unsigned row_off, T* dst) const {
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)((const char*)base +
+                                                          (row_off * (unsigned)sizeof(T) + off[j])),
+          (__attribute__((address_space(3))) void*)((char*)dst + 256 * j), 4, 0, 0);
+  }
+};
 // Waits that are also compiler barriers for memory accesses (the compiler's
 // own wait insertion does not order every LDS read after a pending copy)
 __device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -1246,22 +1254,47 @@ __global__ __launch_bounds__(kWave) void ws_init_kernel(StepScalars* sc) {
 // and cotangents a_B of B(X) = (u, a~, ...) and b of L(X), it writes
 //   G = (dB/dX)^T a_B + (dL_dir/dX)^T b
 // restricted to this direction's terms (in 2D it adds that to G, which
-// holds the y-direction terms). Lanes hold "virtual" cells v =
-// 60 b - 4 + lane (ghost cells included), so every virtual cell in
-// [-2, n+2) is an output lane of exactly one block; contributions to ghost
-// cells go to a side buffer and are folded into their images by
-// ghost_fold_kernel (the transpose of the ghost index map).
+// holds the y-direction terms). Lanes hold "virtual" cells (ghost cells
+// included). Along a periodic line these are images of cells like any other,
+// and the cells [0, n) are the output; otherwise [-2, n+2) is, every cell an
+// output lane of exactly one block, and what a ghost cell receives goes to the
+// cell it is an image of (the transpose of the ghost index map) within the
+// wavefront: the blocks divide the line evenly, so that a ghost cell and its
+// image, at most two cells from the line's end, share one.
+//
+// The along-derivative is carried multiplied by lam h as in the stage kernels
+// (Carried), the cotangents with the inverse factors, which leaves no mesh
+// constant in the arithmetic; the scales are part of VjpScales. Bound by the
+// number of instructions and, the wavefronts of a SIMD starting together, by the
+// latency of the loads at each start; the difference form and its recomputed
+// interpolation (hweno_adjoint_diff.h) leave room for two wavefronts a SIMD.
+// FP64 2D Euler at 512^2, one a set: 44.7 -> 32.1 us a launch (three: 46.4 ->
+// 34.1), and the 5.5 us of a second kernel that added the ghost columns' terms
+// are gone.
+struct VjpScales {
+  double lamh;            // lam h: of the carried derivative
+  double u, a, o;         // of the cotangent b (u, along, other), over dt
+  double vt;              // of the modified derivative (FluxK::vtx)
+};
+template <typename T>
+VjpScales vjp_scales(const Scheme& s, double h, double cb) {
+  const double lam = Carried<T>::lam, mu = Carried<T>::mu;
+  VjpScales k;
+  k.lamh = lam * h;
+  k.u = 0.5 * cb / h;                    // the two halves of the LF flux
+  k.a = 0.5 * cb / (h * (mu * lam * h));
+  k.o = cb / (12.0 * h);                 // (mixed_face)
+  k.vt = point_vt_scale<T>(s) / h;
+  return k;
+}
 template <typename T>
 struct VjpArgs {
   const T* X[3];          // u, along-derivative, other derivative (null in 1D)
   const T* b[3];          // b = cb dt lam_b: the one cotangent state L sees
   const T* a[3][2];       // a_B = sum_k ca_k lam_k (u and along fields)
   double ca[3];
-  double cb;              // multiplied by *dt
   const double* dt;
-  const double* alpha;    // [2]; this pass uses alpha[dir]
-  int dir;
-  int add_identity;       // add the u-part of a_B (B's u-component is the identity)
+  const double* alpha;    // [2]; this pass uses alpha[0]
   int accumulate;         // 2D: add the result and the y-pass's folds to G (else overwrite G)
   T* G[3];                // outputs (u, along, other)
   // with accumulate: the y-pass's strip halos [strip][2 sides][u, w][NC][n]
@@ -1273,12 +1306,11 @@ struct VjpArgs {
   const T* yghost;
   int yR, ystrips;
   int yimg[4], yflip[4], yqj[4], yqs[4];
-  T* ghost;               // [rows][4][3][NC] contributions of virtual cells -2, -1, n, n+1
   int n, rows, plane;
   int bc_lo, bc_hi;
   double gs[2][4];        // fixed ghost states of the low and high side
-  double h, ih;
-  Scheme s;
+  VjpScales sc;
+  PointK pk;
 };
 
 // The y-pass strip whose halo term is aimed at virtual row q: strip j (rows
@@ -1302,28 +1334,67 @@ HWENO_HD int halo_source(int q, int R, int nstrips, int& side) {
   return -1;
 }
 
-template <class Sys, typename T, int D, int NF, int NA, bool WALLS, bool IFACE = false>
-__global__ __launch_bounds__(64) void vjp_row_kernel(VjpArgs<T> A, Sys sy) {
+// Cotangents of the pointwise fluxes of a cell from those of the interfaces
+// i-3/2 .. i+3/2 (F: of the flux, halved, H: of the along-derivative flux,
+// halved and scaled, E: of the mixed one, over 12): the transpose of the central
+// correction (Cd-1)-(DfDh) and of mixed_face.
+template <typename T>
+__device__ __forceinline__ void point_cotangents(T F1, T F0, T Fm1, T Fm2, T H1, T H0, T Hm1, T Hm2,
+                                                 T& gf, T& gh) {
+  constexpr double lam = Carried<T>::lam, mu = Carried<T>::mu;
+  const T s = (F0 + Fm1) - (F1 + Fm2);
+  gf = fma(T(97.0 / 960.0), s,
+           fma(T(2.0 * mu * lam * 697.0 / 5184.0), H1 - Hm2, T(2.0 * mu * lam * 61.0 / 192.0) * (Hm1 - H0)));
+  gh = fma(T(2.0 * 19.0 / (960.0 * lam)), Fm2 - F1, T(2.0 * mu * 37.0 / 864.0) * (H1 + Hm2));
+}
+template <typename T>
+__device__ __forceinline__ T point_cotangent_mixed(T E1, T E0, T Em1, T Em2) {
+  return fma(T(7), E0 + Em1, -(E1 + Em2));
+}
+// Reverse of one side of the LF flux at a face: f(u) + a u, f'(u) v + a v with
+// cotangents gF, gH (a of either sign) -> those of u and v.
+template <int D, class Sys, typename T>
+__device__ __forceinline__ void face_vjp(const Sys& sy, T a, const T (&u)[Sys::NC],
+                                         const T (&v)[Sys::NC], const T (&gF)[Sys::NC],
+                                         const T (&gH)[Sys::NC], T (&gu)[Sys::NC], T (&gv)[Sys::NC]) {
+#pragma unroll
+  for (int c = 0; c < Sys::NC; ++c) {
+    gu[c] = a * gF[c];
+    gv[c] = a * gH[c];
+  }
+  const auto q = sy.prim(u);
+  typename StateBarOf<Sys, T>::type b{};
+  flux_vjp<D>(sy, u, q, gF, b, gu);
+  jac_vjp<D>(sy, u, q, v, gH, b, gu, gv);
+  prim_vjp(sy, u, q, b, gu);
+}
+
+template <class Sys, typename T, int NF, int NA, bool WALLS, bool IFACE = false>
+__global__ __launch_bounds__(64, IFACE ? 1 : 2) void vjp_row_kernel(VjpArgs<T> A, Sys sy) {
   // WALLS: some side of this direction is reflective or fixed
   constexpr int NC = Sys::NC;
-  using Bar = typename BarOf<Sys, T>::type;
   const int lane = threadIdx.x;
   int bx, row;
   xcd_tile(bx, row);
-  const int v = bx * kXOut - 4 + lane;
+  const bool periodic = A.bc_lo == kBcPeriodic;
+  const int lo = periodic ? 0 : -2, total = periodic ? A.n : A.n + 4;
+  const int nb = gridDim.x, wq = total / nb, wr = total % nb;
+  const int start = lo + bx * wq + min(bx, wr), end = start + wq + (bx < wr ? 1 : 0);
+  const int col0 = start - kHalo;
+  const int v = col0 + lane;
   const int g = map_index(v, A.n, A.bc_lo, A.bc_hi);
   const bool interior = v >= 0 && v < A.n;
-  const bool out = lane >= kHalo && lane < kWave - kHalo && v >= -2 && v < A.n + 2;
+  const bool out = lane >= kHalo && v < end;
   const int base = row * A.n;
   const double dtv = A.dt ? *A.dt : 0.0;
-  const T alpha = T(A.alpha[A.dir]);
-  const T h = T(A.h), ih = T(A.ih);
-  const Scheme& s = A.s;
+  const T alpha = T(A.alpha[0]);
 
   // with A.accumulate, the values this pass adds to, and the y-pass halo
   // term aimed at this row (u, w), copied into LDS while the lane works
   __shared__ T gin[NF][NC][kWave];
   __shared__ T yh[2][NC][kWave];
+  __shared__ T fold[4][3][NC];   // what the ghost cells -2, -1, n, n+1 received
+  const RowCopy<T> copy(col0, A.n, lane);
   int hside = 0;
   const int hj = A.accumulate ? halo_source(row, A.yR, A.ystrips, hside) : -1;
   if (A.accumulate) {
@@ -1331,14 +1402,13 @@ __global__ __launch_bounds__(64) void vjp_row_kernel(VjpArgs<T> A, Sys sy) {
     for (int c = 0; c < NC; ++c)
 #pragma unroll
       for (int f = 0; f < NF; ++f)
-        row_to_lds(A.G[f], (unsigned)(c * A.plane + base), bx * kXOut - 4, A.n, &gin[f][c][0], lane);
+        copy(A.G[f], (unsigned)(c * A.plane + base), &gin[f][c][0]);
     if (hj >= 0) {
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-          row_to_lds(A.yhalo, (unsigned)(((hj * 4 + hside * 2 + hf) * NC + c) * A.n),
-                     bx * kXOut - 4, A.n, &yh[hf][c][0], lane);
+          copy(A.yhalo, (unsigned)(((hj * 4 + hside * 2 + hf) * NC + c) * A.n), &yh[hf][c][0]);
     }
   }
   T U[NC], Av[NC], Ov[NC];
@@ -1346,14 +1416,34 @@ __global__ __launch_bounds__(64) void vjp_row_kernel(VjpArgs<T> A, Sys sy) {
   for (int c = 0; c < NC; ++c) {
     const unsigned i = (unsigned)(c * A.plane + base + g);
     U[c] = ld32(A.X[0], i);
-    Av[c] = ld32(A.X[1], i);
+    Av[c] = T(A.sc.lamh) * ld32(A.X[1], i);
     Ov[c] = NF == 3 ? ld32(A.X[2], i) : T(0);
+  }
+  // cotangents; zero at ghost cells that are no images (L and B are defined on
+  // interior cells)
+  T aU[NC], aA[NC], bU[NC], bA[NC], bO[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) { aU[c] = T(0); aA[c] = T(0); bU[c] = T(0); bA[c] = T(0); bO[c] = T(0); }
+  if (interior || periodic) {
+    const T su = T(A.sc.u * dtv), sa = T(A.sc.a * dtv), so = T(A.sc.o * dtv);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const unsigned idx = (unsigned)(c * A.plane + base + g);
+      bU[c] = su * ld32(A.b[0], idx);
+      bA[c] = sa * ld32(A.b[1], idx);
+      if (NF == 3) bO[c] = so * ld32(A.b[2], idx);
+#pragma unroll
+      for (int k = 0; k < NA; ++k) {
+        aU[c] += T(A.ca[k]) * ld32(A.a[k][0], idx);
+        aA[c] += T(A.ca[k] * A.sc.vt) * ld32(A.a[k][1], idx);
+      }
+    }
   }
   if constexpr (WALLS) {
     const bool m = mirrored(v, A.n, A.bc_lo, A.bc_hi);
-    mirror_state<Sys, D>(m, U);
-    mirror_normal_derivative<Sys, D>(m, Av);
-    mirror_state<Sys, D>(m, Ov);
+    mirror_state<Sys, 0>(m, U);
+    mirror_normal_derivative<Sys, 0>(m, Av);
+    mirror_state<Sys, 0>(m, Ov);
     const int fs = fixed_side(v, A.n, A.bc_lo, A.bc_hi);
     if (fs >= 0) {
 #pragma unroll
@@ -1364,117 +1454,114 @@ __global__ __launch_bounds__(64) void vjp_row_kernel(VjpArgs<T> A, Sys sy) {
       }
     }
   }
-  // cotangents; zero at ghost cells (L and B are defined on interior cells)
-  T aU[NC], aA[NC], bU[NC], bA[NC], bO[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) { aU[c] = T(0); aA[c] = T(0); bU[c] = T(0); bA[c] = T(0); bO[c] = T(0); }
-  if (interior) {
-    const T cbt = T(A.cb * dtv);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const unsigned idx = (unsigned)(c * A.plane + base + v);
-      bU[c] = cbt * ld32(A.b[0], idx);
-      bA[c] = cbt * ld32(A.b[1], idx);
-      if (NF == 3) bO[c] = cbt * ld32(A.b[2], idx);
-#pragma unroll
-      for (int k = 0; k < NA; ++k) {
-        aU[c] += T(A.ca[k]) * ld32(A.a[k][0], idx);
-        aA[c] += T(A.ca[k]) * ld32(A.a[k][1], idx);
-      }
-    }
-  }
-  // ---- forward recompute of this cell's interface values
-  T Um[NC], Up[NC], Am[NC], Ap[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    Um[c] = from_prev(U[c]);
-    Up[c] = from_next(U[c]);
-    Am[c] = from_prev(Av[c]);
-    Ap[c] = from_next(Av[c]);
-  }
-  T uR[NC], uL[NC], at_[NC], vR[NC], vL[NC];
-  hweno_cell_b<D, IFACE>(sy, s, A.h, A.ih, sy.prim(U), Um, U, Up, Am, Ap, uR, uL, at_);
-#pragma unroll
-  for (int c = 0; c < NC; ++c) face_derivs(Um[c], U[c], Up[c], Am[c], Ap[c], ih, vR[c], vL[c]);
   // ---- interface cotangents: L_i = -(F_{i+1/2} - F_{i-1/2}) / h
   T lF[NC], lH[NC], lE[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    lF[c] = (from_next(bU[c]) - bU[c]) * ih;
-    lH[c] = (from_next(bA[c]) - bA[c]) * ih;
-    lE[c] = NF == 3 ? (from_next(bO[c]) - bO[c]) * ih : T(0);
+    lF[c] = from_next(bU[c]) - bU[c];
+    lH[c] = from_next(bA[c]) - bA[c];
+    lE[c] = NF == 3 ? from_next(bO[c]) - bO[c] : T(0);
   }
-  // ---- Lax-Friedrichs halves: minus side of x_{v+1/2} (uR, vR) and plus
-  // side of x_{v-1/2} (uL, vL)
-  T guR[NC], gvR[NC], guL[NC], gvL[NC];
-  {
-    T hF[NC], hH[NC], pF[NC], pH[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      hF[c] = T(0.5) * lF[c];
-      hH[c] = T(0.5) * lH[c];
-      pF[c] = T(0.5) * from_prev(lF[c]);
-      pH[c] = T(0.5) * from_prev(lH[c]);
-      guR[c] = alpha * hF[c];
-      gvR[c] = alpha * hH[c];
-      guL[c] = -alpha * pF[c];
-      gvL[c] = -alpha * pH[c];
-    }
-    const auto qr = sy.prim(uR);
-    Bar br{};
-    flux_vjp<D>(sy, uR, qr, hF, br, guR);
-    jac_vjp<D>(sy, uR, qr, vR, hH, br, guR, gvR);
-    prim_vjp(sy, uR, qr, br, guR);
-    const auto ql = sy.prim(uL);
-    Bar bl{};
-    flux_vjp<D>(sy, uL, ql, pF, bl, guL);
-    jac_vjp<D>(sy, uL, ql, vL, pH, bl, guL, gvL);
-    prim_vjp(sy, uL, ql, bl, guL);
-  }
-  // ---- central correction and mixed flux: gather from interfaces v-2..v+1
-  T gU[NC], gA[NC], gO[NC];
+  // ---- the pointwise fluxes f, f'(u) a, f'(u) o of the cell: gather from the
+  // interfaces v-3/2 .. v+3/2
+  T gU[NC], gA[NC], gO[NC], pF[NC], pH[NC];
+  const auto ce = sy.cell_eig(U);
+  typename StateBarOf<Sys, T>::type sb{};
   {
     T gf[NC], gh[NC], ge[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const T F1 = from_next(lF[c]), F0 = lF[c], Fm1 = from_prev(lF[c]), Fm2 = from_prev(Fm1);
-      const T H1 = from_next(lH[c]), H0 = lH[c], Hm1 = from_prev(lH[c]), Hm2 = from_prev(Hm1);
-      gf[c] = T(97.0 / 1920.0) * ((F0 + Fm1) - (F1 + Fm2)) +
-              ih * (T(697.0 / 5184.0) * (H1 - Hm2) + T(61.0 / 192.0) * (Hm1 - H0));
-      gh[c] = T(19.0 / 960.0) * h * (Fm2 - F1) + T(37.0 / 864.0) * (H1 + Hm2);
+      pF[c] = from_prev(lF[c]);
+      pH[c] = from_prev(lH[c]);
+      point_cotangents(from_next(lF[c]), lF[c], pF[c], from_prev(pF[c]), from_next(lH[c]), lH[c],
+                       pH[c], from_prev(pH[c]), gf[c], gh[c]);
+      ge[c] = T(0);
       if constexpr (NF == 3) {
-        const T E1 = from_next(lE[c]), E0 = lE[c], Em1 = from_prev(lE[c]), Em2 = from_prev(Em1);
-        ge[c] = (T(7.0) * (E0 + Em1) - (E1 + Em2)) * T(1.0 / 12.0);
-      } else {
-        ge[c] = T(0);
+        const T Em1 = from_prev(lE[c]);
+        ge[c] = point_cotangent_mixed(from_next(lE[c]), lE[c], Em1, from_prev(Em1));
       }
-      gU[c] = T(0);
+      gU[c] = aU[c];
       gA[c] = T(0);
       gO[c] = T(0);
     }
-    // pointwise f, f'(u) a, f'(u) o at the cell
-    const auto q = sy.prim(U);
-    Bar bq{};
-    flux_vjp<D>(sy, U, q, gf, bq, gU);
-    jac_vjp<D>(sy, U, q, Av, gh, bq, gU, gA);
-    if constexpr (NF == 3) jac_vjp<D>(sy, U, q, Ov, ge, bq, gU, gO);
-    prim_vjp(sy, U, q, bq, gU);
+    flux_vjp<0>(sy, U, ce.q, gf, sb, gU);
+    jac_vjp<0>(sy, U, ce.q, Av, gh, sb, gU, gA);
+    if constexpr (NF == 3) jac_vjp<0>(sy, U, ce.q, Ov, ge, sb, gU, gO);
   }
-  // ---- face derivatives and HWENO of this cell -> its stencil
-  T tm[NC], tc[NC], tp[NC], tAm[NC], tAp[NC];
+  // ---- this cell's face values, the LF halves (minus side of x_{v+1/2}, plus
+  // side of x_{v-1/2}) and the reverse of its HWENO and face derivatives
+  {
+    T E1[NC], E2[NC], S[NC], Dd[NC];
+    T Um[NC], Up[NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    tm[c] = T(0); tc[c] = T(0); tp[c] = T(0); tAm[c] = T(0); tAp[c] = T(0);
-    face_derivs_vjp(gvR[c], gvL[c], ih, tm[c], tc[c], tp[c], tAm[c], tAp[c]);
+    for (int c = 0; c < NC; ++c) {
+      Um[c] = from_prev(U[c]);
+      Up[c] = from_next(U[c]);
+      const T Am = from_prev(Av[c]), Ap = from_next(Av[c]);
+      E1[c] = U[c] - Um[c];
+      E2[c] = Up[c] - U[c];
+      S[c] = Am + Ap;
+      Dd[c] = Am - Ap;
+    }
+    T guR[NC], guL[NC], g1[NC], g2[NC], gS[NC], gD[NC];
+    {
+      T uR[NC], uL[NC], at[NC], vR[NC], vL[NC], gvR[NC], gvL[NC];
+      if constexpr (IFACE)
+        hweno_cell_diff_iface<0>(sy, A.pk, ce, Um, U, Up, E1, E2, S, Dd, uR, uL, at, vR, vL);
+      else
+        hweno_cell_diff<0>(sy, A.pk, ce, U, E1, E2, S, Dd, uR, uL, at, vR, vL);
+      face_vjp<0>(sy, alpha, uR, vR, lF, lH, guR, gvR);
+      face_vjp<0>(sy, -alpha, uL, vL, pF, pH, guL, gvL);
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        face_derivs_diff_vjp(gvR[c], gvL[c], g1[c], g2[c], gS[c], gD[c]);
+    }
+    T tm[NC], tp[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) tm[c] = tp[c] = T(0);
+    if constexpr (IFACE && Sys::kChar)
+      hweno_cell_diff_iface_vjp<0>(sy, A.pk, ce, Um, U, Up, E1, E2, S, Dd, guR, guL, aA, g1, g2, gS, gD,
+                                   tm, gU, tp, sb);
+    else
+      hweno_cell_diff_vjp<0>(sy, A.pk, ce, E1, E2, S, Dd, guR, guL, aA, g1, g2, gS, gD, sb);
+    cell_state_vjp(sy, U, ce, sb, gU);
+    // gather: own + right-neighbour part of the left lane + left part of the right lane
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      tm[c] -= g1[c];
+      tp[c] += g2[c];
+      gU[c] += ((guR[c] + guL[c]) + (g1[c] - g2[c])) + (from_prev(tp[c]) + from_next(tm[c]));
+      gA[c] += from_prev(gS[c] - gD[c]) + from_next(gS[c] + gD[c]);
+      gA[c] *= T(A.sc.lamh);
+    }
   }
-  hweno_cell_vjp_b<D, IFACE, true>(sy, s, A.h, A.ih, Um, U, Up, Am, Ap, guR, guL, aA, tm, tc, tp,
-                                   tAm, tAp);
-  // ---- gather: own + right-neighbour part of the left lane + left part of the right lane
+  if (!periodic && (start < 0 || end > A.n)) {
+    auto ghost_cell = [&](int k) { return k < 2 ? k - 2 : A.n + k - 2; };
+    if (out && !interior) {
+      const int k = v < 0 ? v + 2 : v - A.n + 2;
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    gU[c] += tc[c] + from_prev(tp[c]) + from_next(tm[c]);
-    gA[c] += from_prev(tAp[c]) + from_next(tAm[c]);
-    if (A.add_identity) gU[c] += aU[c];
+      for (int c = 0; c < NC; ++c) {
+        fold[k][0][c] = gU[c];
+        fold[k][1][c] = gA[c];
+        if (NF == 3) fold[k][2][c] = gO[c];
+      }
+    }
+    wait_lds_reads();
+    if (out && interior) {
+      for (int k = 0; k < 4; ++k) {
+        const int w = ghost_cell(k);
+        if (w < start || w >= end || fixed_side(w, A.n, A.bc_lo, A.bc_hi) >= 0) continue;
+        if (map_index(w, A.n, A.bc_lo, A.bc_hi) != v) continue;
+        const bool mir = mirrored(w, A.n, A.bc_lo, A.bc_hi);
+        auto add = [&](int f, T (&G)[NC]) {
+#pragma unroll
+          for (int c = 0; c < NC; ++c) G[c] += mir && mirror_flips(0, f, c) ? -fold[k][f][c] : fold[k][f][c];
+        };
+        add(0, gU);
+        add(1, gA);
+        if (NF == 3) add(2, gO);
+      }
+    }
   }
   unsigned gmask = 0;   // y ghost rows folding into this row
   if (A.accumulate) {
@@ -1482,53 +1569,42 @@ __global__ __launch_bounds__(64) void vjp_row_kernel(VjpArgs<T> A, Sys sy) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) gmask |= A.yimg[k] == row ? 1u << k : 0u;
   }
-  if (out) {
-    if (interior) {
+  if (out && interior) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const unsigned idx = (unsigned)(c * A.plane + base + v);
-        if (A.accumulate) {
-          gU[c] += gin[0][c][lane];
-          gA[c] += gin[1][c][lane];
-          if (NF == 3) gO[c] += gin[NF - 1][c][lane];
-          if (hj >= 0) {
-            gU[c] += yh[0][c][lane];
-            if (NF == 3) gO[c] += yh[1][c][lane];
-          }
-          // the y ghost rows whose image is this row (edge rows only), each
-          // with the halo term aimed at it, with the y walls' sign rules
-          if (gmask) {
+    for (int c = 0; c < NC; ++c) {
+      const unsigned idx = (unsigned)(c * A.plane + base + v);
+      if (A.accumulate) {
+        gU[c] += gin[0][c][lane];
+        gA[c] += gin[1][c][lane];
+        if (NF == 3) gO[c] += gin[NF - 1][c][lane];
+        if (hj >= 0) {
+          gU[c] += yh[0][c][lane];
+          if (NF == 3) gO[c] += yh[1][c][lane];
+        }
+        // the y ghost rows whose image is this row (edge rows only), each
+        // with the halo term aimed at it, with the y walls' sign rules
+        if (gmask) {
 #pragma unroll 1
-            for (int k = 0; k < 4; ++k) {
-              if (!((gmask >> k) & 1u)) continue;
-              const int qj = A.yqj[k], qs = A.yqs[k];
-              T gv[3];
+          for (int k = 0; k < 4; ++k) {
+            if (!((gmask >> k) & 1u)) continue;
+            const int qj = A.yqj[k], qs = A.yqs[k];
+            T gv[3];
 #pragma unroll
-              for (int f = 0; f < 3; ++f) {
-                gv[f] = A.yghost[((size_t)(k * 3 + f) * NC + c) * A.n + v];
-                if (qj >= 0 && f != 1)
-                  gv[f] += A.yhalo[((size_t)(qj * 4 + qs * 2 + (f == 0 ? 0 : 1)) * NC + c) * A.n + v];
-                if (A.yflip[k] && mirror_flips(1, f, c)) gv[f] = -gv[f];
-              }
-              gU[c] += gv[0];
-              gA[c] += gv[1];
-              if (NF == 3) gO[c] += gv[2];
+            for (int f = 0; f < 3; ++f) {
+              gv[f] = A.yghost[((size_t)(k * 3 + f) * NC + c) * A.n + v];
+              if (qj >= 0 && f != 1)
+                gv[f] += A.yhalo[((size_t)(qj * 4 + qs * 2 + (f == 0 ? 0 : 1)) * NC + c) * A.n + v];
+              if (A.yflip[k] && mirror_flips(1, f, c)) gv[f] = -gv[f];
             }
+            gU[c] += gv[0];
+            gA[c] += gv[1];
+            if (NF == 3) gO[c] += gv[2];
           }
         }
-        st32(A.G[0], idx, gU[c]);
-        st32(A.G[1], idx, gA[c]);
-        if (NF == 3) st32(A.G[2], idx, gO[c]);
       }
-    } else {
-      const int slot = v < 0 ? v + 2 : v - A.n + 2;
-      T* gp = A.ghost + ((size_t)row * 4 + slot) * 3 * NC;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        gp[c] = gU[c];
-        gp[NC + c] = gA[c];
-        gp[2 * NC + c] = gO[c];
-      }
+      st32(A.G[0], idx, gU[c]);
+      st32(A.G[1], idx, gA[c]);
+      if (NF == 3) st32(A.G[2], idx, gO[c]);
     }
   }
 }
@@ -1545,13 +1621,15 @@ __global__ __launch_bounds__(64) void vjp_row_kernel(VjpArgs<T> A, Sys sy) {
 // to the halo terms and is stored to G (the x-pass, which runs next, adds
 // its own result). The next row's inputs are copied into LDS while a row is
 // computed, so a row's loads wait on memory only once per strip.
+// Bound by the number of instructions (an iteration of the FP64 Euler kernel:
+// 1855 VALU instructions, with the term-by-term reverse 2770): 512^2 49.5 -> 38.7
+// us a launch.
 template <typename T>
 struct VjpYArgs {
   const T* X[3];          // u, v, w
   const T* b[3];          // b = cb dt lam_b (u, v, w)
   const T* aw[3];         // w fields of the a sets: a_w = sum_k ca_k lam_k,w
   double ca[3];
-  double cb;              // multiplied by *dt
   int na;                 // number of a sets (1 or 3)
   const double* dt;
   const double* alpha;    // [2]; uses alpha[1]
@@ -1561,13 +1639,13 @@ struct VjpYArgs {
   int nx, ny, rows, plane;
   int bc_lo, bc_hi;
   double gs[2][4];        // fixed ghost states of the low and high side (y)
-  Scheme s;
+  VjpScales sc;           // along y
+  PointK pk;
 };
 
 template <class Sys, typename T, bool WALLS, bool IFACE = false>
 __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
   constexpr int NC = Sys::NC;
-  using Bar = typename BarOf<Sys, T>::type;
   const int lane = threadIdx.x;
   const int x = blockIdx.x * kWave + lane;
   const bool colok = x < A.nx;
@@ -1575,82 +1653,98 @@ __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
   const int o1 = min(o0 + A.rows, A.ny + 2);
   const double dtv = A.dt ? *A.dt : 0.0;
   const T alpha = T(A.alpha[1]);
-  const Scheme& s = A.s;
-  const T h = T(s.dy), ih = T(s.idy);
-  const T cbt = T(A.cb * dtv);
+  const T su = T(A.sc.u * dtv), sv = T(A.sc.o * dtv), sw = T(A.sc.a * dtv), lamh = T(A.sc.lamh);
   // interface cotangents (G, theta, xi) of the 3 previous interfaces, slot k mod 3
   __shared__ T lring[3][3][NC][kWave];
   // the next row's inputs, copied in while the current row is computed:
   // u, v, w, b_u, b_v, b_w, then the a_w sets
   __shared__ T stage[9][NC][kWave];
-  const int col0 = blockIdx.x * kWave;
+  const RowCopy<T> copy(blockIdx.x * kWave, A.nx, lane);
+  // (v of row rr - 2 and the a_w of row rr - 1, which is when they are used)
   auto fetch = [&](int rr) {
     const int g = map_index(rr, A.ny, A.bc_lo, A.bc_hi);
-    const bool in = rr >= 0 && rr < A.ny;
+    const int g2 = map_index(rr - 2, A.ny, A.bc_lo, A.bc_hi);
+    const bool in = rr >= 0 && rr < A.ny, in1 = rr >= 1 && rr <= A.ny;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const unsigned off = (unsigned)(c * A.plane + g * A.nx);
-#pragma unroll
-      for (int f = 0; f < 3; ++f) row_to_lds(A.X[f], off, col0, A.nx, &stage[f][c][0], lane);
+      copy(A.X[0], off, &stage[0][c][0]);
+      copy(A.X[1], (unsigned)(c * A.plane + g2 * A.nx), &stage[1][c][0]);
+      copy(A.X[2], off, &stage[2][c][0]);
       if (in) {
 #pragma unroll
-        for (int f = 0; f < 3; ++f) row_to_lds(A.b[f], off, col0, A.nx, &stage[3 + f][c][0], lane);
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-          if (k < A.na) row_to_lds(A.aw[k], off, col0, A.nx, &stage[6 + k][c][0], lane);
+        for (int f = 0; f < 3; ++f) copy(A.b[f], off, &stage[3 + f][c][0]);
       }
     }
+    if (in1) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k < A.na) {
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+            copy(A.aw[k], (unsigned)(c * A.plane + (rr - 1) * A.nx), &stage[6 + k][c][0]);
+        }
+    }
   };
-  T Ua[NC], Ub[NC], Va[NC], Vb[NC], Wa[NC], Wb[NC];   // rows r-2, r-1
-  T bU1[NC], bV1[NC], bW1[NC], aW1[NC];              // cotangents of row r-1
+  T Ua[NC], Ub[NC], Wa[NC], Wb[NC];      // rows r-2, r-1
+  T bU1[NC], bV1[NC], bW1[NC];           // cotangents of row r-1
   T accUa[NC], accWa[NC], accUb[NC], accWb[NC];      // HWENO-reverse sums of rows r-2, r-1
 #pragma unroll
   for (int c = 0; c < NC; ++c) { accUa[c] = T(0); accWa[c] = T(0); accUb[c] = T(0); accWb[c] = T(0); }
   fetch(o0 - 2);
   for (int r = o0 - 2; r < o1 + 2; ++r) {
-    const bool inrow = r >= 0 && r < A.ny;
+    const bool inrow = r >= 0 && r < A.ny, inrow1 = r >= 1 && r <= A.ny;
     wait_copies();
-    T Uc[NC], Vc[NC], Wc[NC], bUc[NC], bVc[NC], bWc[NC], aWc[NC];
+    T Uc[NC], Va[NC], Wc[NC], bUc[NC], bVc[NC], bWc[NC], aW1[NC];   // v of row r-2, a_w of row r-1
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       Uc[c] = stage[0][c][lane];
-      Vc[c] = stage[1][c][lane];
-      Wc[c] = stage[2][c][lane];
-      bUc[c] = T(0); bVc[c] = T(0); bWc[c] = T(0); aWc[c] = T(0);
+      Va[c] = stage[1][c][lane];
+      Wc[c] = lamh * stage[2][c][lane];
+      bUc[c] = T(0); bVc[c] = T(0); bWc[c] = T(0); aW1[c] = T(0);
       if (inrow) {
-        bUc[c] = cbt * stage[3][c][lane];
-        bVc[c] = cbt * stage[4][c][lane];
-        bWc[c] = cbt * stage[5][c][lane];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-          if (k < A.na) aWc[c] += T(A.ca[k]) * stage[6 + k][c][lane];
+        bUc[c] = su * stage[3][c][lane];
+        bVc[c] = sv * stage[4][c][lane];
+        bWc[c] = sw * stage[5][c][lane];
       }
+    }
+    if (inrow1) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k < A.na) {
+          const T ca = T(A.ca[k] * A.sc.vt);
+#pragma unroll
+          for (int c = 0; c < NC; ++c) aW1[c] += ca * stage[6 + k][c][lane];
+        }
     }
     wait_lds_reads();
     if (r + 1 < o1 + 2) fetch(r + 1);
     if constexpr (WALLS) {
       if (mirrored(r, A.ny, A.bc_lo, A.bc_hi)) {
         mirror_state<Sys, 1>(true, Uc);
-        mirror_state<Sys, 1>(true, Vc);
         mirror_normal_derivative<Sys, 1>(true, Wc);
       }
+      if (mirrored(r - 2, A.ny, A.bc_lo, A.bc_hi)) mirror_state<Sys, 1>(true, Va);
       const int fs = fixed_side(r, A.ny, A.bc_lo, A.bc_hi);
       if (fs >= 0) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           Uc[c] = T(A.gs[fs][c]);
-          Vc[c] = T(0);
           Wc[c] = T(0);
         }
+      }
+      if (fixed_side(r - 2, A.ny, A.bc_lo, A.bc_hi) >= 0) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) Va[c] = T(0);
       }
     }
     // interface (r-1)+1/2: L_j = -(F_{j+1/2} - F_{j-1/2}) / dy
     T lG[NC], lT[NC], lX[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      lG[c] = (bUc[c] - bU1[c]) * ih;
-      lT[c] = (bWc[c] - bW1[c]) * ih;
-      lX[c] = (bVc[c] - bV1[c]) * ih;
+      lG[c] = bUc[c] - bU1[c];
+      lT[c] = bWc[c] - bW1[c];
+      lX[c] = bVc[c] - bV1[c];
     }
     const int s1 = ((r - 1) % 3 + 3) % 3;        // slot of interface r-1 (and r-4)
     const int s2 = s1 == 0 ? 2 : s1 - 1;          // interface r-2
@@ -1661,49 +1755,48 @@ __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
     if (r >= o0 + 1 && r <= o1) {
       // reverse of cell r-1's faces: top face -> interface (r-1)+1/2 (minus
       // side), bottom face -> interface (r-2)+1/2 (plus side)
-      T uT[NC], uB[NC], wt_[NC], wT[NC], wB[NC];
-      hweno_cell_b<1, IFACE>(sy, s, s.dy, s.idy, sy.prim(Ub), Ua, Ub, Uc, Wa, Wc, uT, uB, wt_);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) face_derivs(Ua[c], Ub[c], Uc[c], Wa[c], Wc[c], ih, wT[c], wB[c]);
-      T hG[NC], hT[NC], pG[NC], pT[NC], guT[NC], gwT[NC], guB[NC], gwB[NC];
+      const auto ce = sy.cell_eig(Ub);
+      typename StateBarOf<Sys, T>::type sb{};
+      T E1[NC], E2[NC], S[NC], Dd[NC];
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        hG[c] = T(0.5) * lG[c];
-        hT[c] = T(0.5) * lT[c];
-        pG[c] = T(0.5) * lring[s2][0][c][lane];
-        pT[c] = T(0.5) * lring[s2][1][c][lane];
-        guT[c] = alpha * hG[c];
-        gwT[c] = alpha * hT[c];
-        guB[c] = -alpha * pG[c];
-        gwB[c] = -alpha * pT[c];
+        E1[c] = Ub[c] - Ua[c];
+        E2[c] = Uc[c] - Ub[c];
+        S[c] = Wa[c] + Wc[c];
+        Dd[c] = Wa[c] - Wc[c];
       }
+      T guT[NC], guB[NC], g1[NC], g2[NC], gS[NC], gD[NC];
       {
-        const auto qt = sy.prim(uT);
-        Bar bt{};
-        flux_vjp<1>(sy, uT, qt, hG, bt, guT);
-        jac_vjp<1>(sy, uT, qt, wT, hT, bt, guT, gwT);
-        prim_vjp(sy, uT, qt, bt, guT);
-        const auto qb = sy.prim(uB);
-        Bar bb{};
-        flux_vjp<1>(sy, uB, qb, pG, bb, guB);
-        jac_vjp<1>(sy, uB, qb, wB, pT, bb, guB, gwB);
-        prim_vjp(sy, uB, qb, bb, guB);
+        T uT[NC], uB[NC], wt_[NC], wT[NC], wB[NC], gwT[NC], gwB[NC], pG[NC], pT[NC];
+        if constexpr (IFACE)
+          hweno_cell_diff_iface<1>(sy, A.pk, ce, Ua, Ub, Uc, E1, E2, S, Dd, uT, uB, wt_, wT, wB);
+        else
+          hweno_cell_diff<1>(sy, A.pk, ce, Ub, E1, E2, S, Dd, uT, uB, wt_, wT, wB);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          pG[c] = lring[s2][0][c][lane];
+          pT[c] = lring[s2][1][c][lane];
+        }
+        face_vjp<1>(sy, alpha, uT, wT, lG, lT, guT, gwT);
+        face_vjp<1>(sy, -alpha, uB, wB, pG, pT, guB, gwB);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          face_derivs_diff_vjp(gwT[c], gwB[c], g1[c], g2[c], gS[c], gD[c]);
       }
-      T tm[NC], tc[NC], tWm[NC];
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (IFACE && Sys::kChar)
+        hweno_cell_diff_iface_vjp<1>(sy, A.pk, ce, Ua, Ub, Uc, E1, E2, S, Dd, guT, guB, aW1, g1, g2, gS,
+                                     gD, accUa, accUb, accUc, sb);
+      else
+        hweno_cell_diff_vjp<1>(sy, A.pk, ce, E1, E2, S, Dd, guT, guB, aW1, g1, g2, gS, gD, sb);
+      cell_state_vjp(sy, Ub, ce, sb, accUb);
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        tm[c] = T(0); tc[c] = T(0); tWm[c] = T(0);
-        face_derivs_vjp(gwT[c], gwB[c], ih, tm[c], tc[c], accUc[c], tWm[c], accWc[c]);
-      }
-      // the fused point reverse (one forward evaluation fewer) pays in FP32;
-      // in FP64 its live intermediates spill (backward 76 -> 97 ms at 512^2)
-      hweno_cell_vjp_b<1, IFACE, std::is_same<T, float>::value>(
-          sy, s, s.dy, s.idy, Ua, Ub, Uc, Wa, Wc, guT, guB, aW1, tm, tc, accUc, tWm, accWc);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        accUa[c] += tm[c];
-        accWa[c] += tWm[c];
-        accUb[c] += tc[c];
+        accUa[c] -= g1[c];
+        accUb[c] += (guT[c] + guB[c]) + (g1[c] - g2[c]);
+        accUc[c] += g2[c];
+        accWa[c] += gS[c] + gD[c];
+        accWc[c] += gS[c] - gD[c];
       }
     }
     if (r == o0 + 1 && colok) {
@@ -1713,7 +1806,7 @@ __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         hb[(0 * NC + c) * A.nx] = accUa[c];
-        hb[(1 * NC + c) * A.nx] = accWa[c];
+        hb[(1 * NC + c) * A.nx] = lamh * accWa[c];
       }
     }
     if (r >= o0 + 2) {
@@ -1725,20 +1818,20 @@ __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
         const T G1 = lG[c], G0 = lring[s2][0][c][lane], Gm1 = lring[s3][0][c][lane], Gm2 = lring[s1][0][c][lane];
         const T T1 = lT[c], T0 = lring[s2][1][c][lane], Tm1 = lring[s3][1][c][lane], Tm2 = lring[s1][1][c][lane];
         const T X1 = lX[c], X0 = lring[s2][2][c][lane], Xm1 = lring[s3][2][c][lane], Xm2 = lring[s1][2][c][lane];
-        gg[c] = T(97.0 / 1920.0) * ((G0 + Gm1) - (G1 + Gm2)) +
-                ih * (T(697.0 / 5184.0) * (T1 - Tm2) + T(61.0 / 192.0) * (Tm1 - T0));
-        gt[c] = T(19.0 / 960.0) * h * (Gm2 - G1) + T(37.0 / 864.0) * (T1 + Tm2);
-        gx[c] = (T(7.0) * (X0 + Xm1) - (X1 + Xm2)) * T(1.0 / 12.0);
+        point_cotangents(G1, G0, Gm1, Gm2, T1, T0, Tm1, Tm2, gg[c], gt[c]);
+        gx[c] = point_cotangent_mixed(X1, X0, Xm1, Xm2);
       }
       T gU[NC], gV[NC], gW[NC];
 #pragma unroll
       for (int c = 0; c < NC; ++c) { gU[c] = accUa[c]; gW[c] = accWa[c]; gV[c] = T(0); }
       const auto q = sy.prim(Ua);
-      Bar bq{};
+      typename StateBarOf<Sys, T>::type bq{};
       flux_vjp<1>(sy, Ua, q, gg, bq, gU);
       jac_vjp<1>(sy, Ua, q, Wa, gt, bq, gU, gW);
       jac_vjp<1>(sy, Ua, q, Va, gx, bq, gU, gV);
       prim_vjp(sy, Ua, q, bq, gU);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) gW[c] *= lamh;
       if (colok) {
         if (o >= 0 && o < A.ny) {
 #pragma unroll
@@ -1767,9 +1860,8 @@ __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
       lring[s1][1][c][lane] = lT[c];
       lring[s1][2][c][lane] = lX[c];
       Ua[c] = Ub[c]; Ub[c] = Uc[c];
-      Va[c] = Vb[c]; Vb[c] = Vc[c];
       Wa[c] = Wb[c]; Wb[c] = Wc[c];
-      bU1[c] = bUc[c]; bV1[c] = bVc[c]; bW1[c] = bWc[c]; aW1[c] = aWc[c];
+      bU1[c] = bUc[c]; bV1[c] = bVc[c]; bW1[c] = bWc[c];
       accUa[c] = accUb[c]; accWa[c] = accWb[c];
       accUb[c] = accUc[c]; accWb[c] = accWc[c];
     }
@@ -1781,35 +1873,8 @@ __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       hb[(2 * NC + c) * A.nx] = accUa[c];
-      hb[(3 * NC + c) * A.nx] = accWa[c];
+      hb[(3 * NC + c) * A.nx] = lamh * accWa[c];
     }
-  }
-}
-
-// Adds the ghost-cell contributions to the cells they were copied from (with
-// the reflective sign rules where a wall mirrors them), in a fixed order (one
-// thread per line, field and component).
-template <typename T>
-__global__ __launch_bounds__(256) void ghost_fold_kernel(T* __restrict__ G0, T* __restrict__ G1,
-                                                         T* __restrict__ G2,
-                                                         const T* __restrict__ ghost, int n, int rows,
-                                                         int plane, int nc, int nf, int lo, int hi) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int total = rows * nf * nc;
-  if (t >= total) return;
-  const int c = t % nc;
-  const int f = (t / nc) % nf;
-  const int row = t / (nc * nf);
-  T* G = (f == 0 ? G0 : (f == 1 ? G1 : G2)) + (size_t)c * plane + (size_t)row * n;
-  const T* gp = ghost + (size_t)row * 4 * 3 * nc + f * nc + c;
-  const int gs = 3 * nc;
-  const T gv[4] = {gp[0], gp[gs], gp[2 * gs], gp[3 * gs]};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {   // virtual cells -2, -1, n, n+1
-    const int v = k < 2 ? k - 2 : n + k - 2;
-    if (fixed_side(v, n, lo, hi) >= 0) continue;    // fixed states: no image
-    const bool neg = mirrored(v, n, lo, hi) && mirror_flips(0, f, c);
-    G[map_index(v, n, lo, hi)] += neg ? -gv[k] : gv[k];
   }
 }
 
@@ -1954,8 +2019,8 @@ Geometry geometry(const hweno_problem* p) {
 // Workspace: scalars | per-block partial maxima | states | adjoint scratch.
 // States are stored densely ([field][comp][ny][nx]); each region starts on a
 // 256-byte boundary. Regions: X^(1), X^(2), the RK base derivatives
-// (V~^n[, W~^n]), and for the adjoint: lambda^(2), lambda^(1), the
-// ghost-cell side buffers and (2D) the y-pass strip halo terms.
+// (V~^n[, W~^n]), and for the adjoint: lambda^(2), lambda^(1) and, in 2D, the
+// y-pass's ghost rows and strip halo terms.
 struct WsLayout {
   StepScalars* sc;
   double* partial;
@@ -1964,7 +2029,6 @@ struct WsLayout {
   char* base;
   char* lam2;
   char* lam1;
-  char* ghost;     // x-pass ghost columns [ny][4][3][NC]
   char* ghost_y;   // y-pass ghost rows [4][3][NC][nx]
   char* halo;      // y-pass strip halo terms [strips][2][2][NC][nx]
   size_t state_bytes;
@@ -1972,9 +2036,6 @@ struct WsLayout {
 
 size_t state_bytes(const Geometry& g) { return align_up((size_t)g.nf * g.nc * g.plane * g.esize, 256); }
 size_t base_bytes(const Geometry& g) { return align_up((size_t)(g.nf - 1) * g.nc * g.plane * g.esize, 256); }
-size_t ghost_x_bytes(const hweno_problem* p, const Geometry& g) {
-  return align_up((size_t)p->ny * 4 * 3 * g.nc * g.esize, 256);
-}
 size_t ghost_y_bytes(const hweno_problem* p, const Geometry& g) {
   return p->dim == 2 ? align_up((size_t)p->nx * 4 * 3 * g.nc * g.esize, 256) : 0;
 }
@@ -1986,7 +2047,7 @@ size_t halo_bytes(const hweno_problem* p, const Geometry& g) {
   return align_up(strips * 4 * g.nc * (size_t)p->nx * g.esize, 256);
 }
 size_t ghost_bytes(const hweno_problem* p, const Geometry& g) {
-  return ghost_x_bytes(p, g) + ghost_y_bytes(p, g) + halo_bytes(p, g);
+  return ghost_y_bytes(p, g) + halo_bytes(p, g);
 }
 size_t ws_total(const hweno_problem* p, const Geometry& g) {
   return kScalarBytes + kPartialBytes + 4 * state_bytes(g) + base_bytes(g) + ghost_bytes(p, g);
@@ -2028,8 +2089,7 @@ WsLayout ws_layout(const hweno_problem* p, void* ws, const Geometry& g) {
   w.base = w.x2 + w.state_bytes;
   w.lam2 = w.base + base_bytes(g);
   w.lam1 = w.lam2 + w.state_bytes;
-  w.ghost = w.lam1 + w.state_bytes;
-  w.ghost_y = w.ghost + ghost_x_bytes(p, g);
+  w.ghost_y = w.lam1 + w.state_bytes;
   w.halo = w.ghost_y + ghost_y_bytes(p, g);
   return w;
 }
@@ -2284,8 +2344,9 @@ hweno_status launch_speed_partial(const hweno_problem* p, const T* U, const Sys&
   return check_launch();
 }
 
-// One VJP of a stage: the x-pass writes out[], the 2D y-pass marches up
-// column strips and adds to it; each pass then folds its ghost cells.
+// One VJP of a stage: in 2D the y-pass marches up column strips and writes
+// out[], then the x-pass adds its terms and the y-pass's strip halos and ghost
+// rows; in 1D the x-pass alone writes it.
 struct Cot {
   const void* b[3];       // the flux cotangent state (u, v, w; w null in 1D), scaled by cb dt
   double cb;
@@ -2300,6 +2361,7 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
                         const double* alpha, const double* dt, T* out[3], hipStream_t st) {
   constexpr int NC = Sys::NC;
   const Scheme sc = make_scheme(p);
+  const PointK pk = point_k(sc, Carried<T>::lam, point_vt_scale<T>(sc));
   const int nx = p->nx, ny = p->ny, plane = nx * ny;
   // the interface basis changes only the per-cell reverse (three bases)
   const bool iface = Sys::kChar && p->char_basis == HWENO_BASIS_INTERFACE;
@@ -2318,7 +2380,6 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
       A.ca[k] = cot.ca[k];
     }
     A.na = cot.na;
-    A.cb = cot.cb;
     A.dt = dt;
     A.alpha = alpha;
     for (int f = 0; f < 3; ++f) A.G[f] = out[f];
@@ -2333,7 +2394,8 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
       A.gs[0][c] = p->bc_state[2][c];
       A.gs[1][c] = p->bc_state[3][c];
     }
-    A.s = sc;
+    A.sc = vjp_scales<T>(sc, sc.dy, cot.cb);
+    A.pk = pk;
     // strips of at least kMinStripRows rows (the halo buffer is sized for
     // that); warm-up: four rows of loads
     bool walls = false;
@@ -2364,8 +2426,7 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
     ystrip_rows = A.rows;
     ystrips = nstrips;
   }
-  // x-pass (in 2D after the y-pass, adding to its result), then the fold
-  // of its ghost columns
+  // x-pass (in 2D after the y-pass, adding to its result)
   {
     VjpArgs<T> A;
     std::memset(&A, 0, sizeof(A));
@@ -2378,11 +2439,8 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
       A.a[k][1] = (const T*)cot.a[k][1];
       A.ca[k] = cot.ca[k];
     }
-    A.cb = cot.cb;
     A.dt = dt;
     A.alpha = alpha;
-    A.dir = 0;
-    A.add_identity = 1;
     A.accumulate = DIM == 2;   // in 2D the y-pass has written out
     if (DIM == 2) {
       A.yhalo = (const T*)wl.halo;
@@ -2398,7 +2456,6 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
       }
     }
     for (int f = 0; f < 3; ++f) A.G[f] = out[f];
-    A.ghost = (T*)wl.ghost;
     A.n = nx;
     A.rows = ny;
     A.plane = plane;
@@ -2408,18 +2465,18 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
       A.gs[0][c] = p->bc_state[0][c];
       A.gs[1][c] = p->bc_state[1][c];
     }
-    A.h = sc.dx;
-    A.ih = sc.idx;
-    A.s = sc;
-    dim3 grid((nx + 4 + kXOut - 1) / kXOut, ny);
+    A.sc = vjp_scales<T>(sc, sc.dx, cot.cb);
+    A.pk = pk;
+    const int total = p->bc[0] == HWENO_PERIODIC ? nx : nx + 4;
+    dim3 grid((total + kXOut - 1) / kXOut, ny);
     auto special = [](int b) { return b == HWENO_REFLECTIVE || b == HWENO_DIRICHLET; };
     const bool xwalls = special(p->bc[0]) || special(p->bc[1]);
     auto go = [&](auto walls, auto ifc) {
       constexpr bool W = decltype(walls)::value, I = decltype(ifc)::value;
       if (cot.na == 1)
-        vjp_row_kernel<Sys, T, 0, DIM + 1, 1, W, I><<<grid, kWave, 0, st>>>(A, sy);
+        vjp_row_kernel<Sys, T, DIM + 1, 1, W, I><<<grid, kWave, 0, st>>>(A, sy);
       else
-        vjp_row_kernel<Sys, T, 0, DIM + 1, 3, W, I><<<grid, kWave, 0, st>>>(A, sy);
+        vjp_row_kernel<Sys, T, DIM + 1, 3, W, I><<<grid, kWave, 0, st>>>(A, sy);
     };
     auto go_w = [&](auto ifc) {
       if (xwalls)
@@ -2436,13 +2493,6 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
       go_w(std::false_type{});
     }
     if (check_launch() != HWENO_OK) return HWENO_EDEVICE;
-    {
-      const int tot = ny * g.nf * NC;
-      ghost_fold_kernel<T><<<(tot + 255) / 256, 256, 0, st>>>(out[0], out[1], out[2], (const T*)wl.ghost,
-                                                             nx, ny, plane, NC, g.nf,
-                                                             p->bc[0], p->bc[1]);
-      if (check_launch() != HWENO_OK) return HWENO_EDEVICE;
-    }
   }
   if constexpr (DIM == 2) {
     if (Sys::kChar && NC == 4 && p->gravity != 0.0) {

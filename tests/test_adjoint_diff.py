@@ -1,0 +1,70 @@
+"""The adjoint kernels' reverse functions (difference form) against the
+term-by-term ones, built for and run on the host; and on the GPU the two passes
+of the adjoint against each other where their handling of the domain's ends
+differs."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_difference_form_matches_term_by_term_form(tmp_path):
+    hipcc = shutil.which('hipcc') or '/opt/rocm/bin/hipcc'
+    if not os.path.exists(hipcc):
+        pytest.skip('hipcc not available')
+    exe = str(tmp_path / 'adjoint_diff_check')
+    subprocess.run([hipcc, '-O1', '-std=c++17', '--offload-arch=gfx950',
+                    f'-I{os.path.join(ROOT, "paper_2411_11229_amd", "csrc")}',
+                    os.path.join(ROOT, 'tests', 'cpu_math', 'adjoint_diff_check.cpp'), '-o', exe],
+                   check=True, capture_output=True, text=True)
+    res = subprocess.run([exe], capture_output=True, text=True)
+    print(res.stdout)
+    assert res.returncode == 0 and 'ALL OK' in res.stdout, res.stdout + res.stderr
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize('basis', ['cell', 'interface'])
+@pytest.mark.parametrize('n', [5, 6, 56, 57, 60, 61, 116, 117, 121])
+@pytest.mark.parametrize('ends', [('periodic',) * 2, ('reflective', 'transmissive'),
+                                  ('transmissive', 'reflective')], ids=lambda e: e[0][:5])
+def test_adjoint_passes_agree_on_the_transposed_problem(ends, n, basis):
+    """The x-pass divides a line of n cells evenly over wavefronts of at most 60
+    (or n + 4 with ghost cells) and returns what ghost cells receive within
+    the wavefront; the y-pass goes through ghost rows. The adjoint of the
+    transposed problem swaps the two. Same terms in another order: agreement to
+    1e-9 of each field's largest (rounding 1e-16, times the few 1e5 by which
+    the weights' derivatives exceed the result)."""
+    from paper_2411_11229_amd import hweno as H
+    from paper_2411_11229_amd import workloads as WL
+    print(f'n {n} {ends} {basis}', flush=True)
+    m = 9
+    w = WL.with_bc(WL.euler2d_smooth(n, seed=3200 + n, ny=m, amp=0.02), tuple(ends) + ('periodic',) * 2)
+    perm = [0, 2, 1, 3]
+    flip = lambda a: np.ascontiguousarray(a[perm].transpose(0, 2, 1))
+    rng = np.random.default_rng(n)
+    lam = [rng.standard_normal(w.U.shape) for _ in range(3)]
+    alphas = np.array([1.7, 1.5, 1.8, 1.4, 1.75, 1.45])
+    outs = []
+    for turned in (False, True):
+        kw = w.problem_kwargs()
+        X, lm, al = [w.U, w.V, w.W], lam, alphas
+        if turned:
+            kw.update(nx=m, ny=n, dx=w.dy, dy=w.dx, bc=tuple(w.bc[2:]) + tuple(w.bc[:2]))
+            X = [flip(w.U), flip(w.W), flip(w.V)]
+            lm = [flip(lam[0]), flip(lam[2]), flip(lam[1])]
+            al = alphas.reshape(3, 2)[:, ::-1].copy().reshape(-1)
+        dev = lambda a: torch.tensor(a, dtype=torch.float64, device='cuda')
+        s = H.Solver(H.Problem(**kw, basis=basis))
+        out = [dev(np.zeros_like(a)) for a in X]
+        s.adjoint_step(*[dev(a) for a in X], dev(np.array([0.1 * w.dx])), dev(al),
+                       [dev(a) for a in lm], out)
+        o = [a.cpu().numpy() for a in out]
+        outs.append([flip(o[0]), flip(o[2]), flip(o[1])] if turned else o)
+    for name, a, b in zip('UVW', *outs):
+        assert np.isfinite(a).all()
+        assert np.abs(a - b).max() <= 1e-9 * np.abs(a).max(), name
