@@ -1878,6 +1878,216 @@ __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
   }
 }
 
+// The same for small grids: one wavefront per row, as in the stage's tile kernel.
+// A block of H + 2 wavefronts takes the H virtual rows [o0, o0 + H); wavefront w
+// reverses the HWENO of row q = o0 - 1 + w and, in the inner ones, the pointwise
+// fluxes of the row. The scaled cotangents b of the rows meet in LDS before,
+// what the cells add to the rows below and above them after the work. A row's
+// sums are complete within the block: no halo terms. Bound by latency (the start,
+// the loads, one row's serial arithmetic) in place of the marcher's H + 4 rows
+// one after the other; measured at the rule (tile_rows).
+template <int NC, typename T>
+constexpr size_t vjp_tile_lds(int H) {
+  return ((size_t)(H + 4) * 3 + (size_t)(H + 2) * 4) * NC * kWave * sizeof(T);
+}
+template <class Sys, typename T, bool WALLS, bool IFACE = false>
+__global__ __launch_bounds__(kTileThreads, 2) void vjp_y_tile_kernel(VjpYArgs<T> A, Sys sy) {
+  constexpr int NC = Sys::NC;
+  constexpr int R = NC * kWave;                    // values of one field of one row
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int bx, by;
+  xcd_tile(bx, by);
+  const int x = bx * kWave + lane;
+  const bool colok = x < A.nx;
+  const int col = min(x, A.nx - 1);
+  const int o0 = -2 + by * A.rows;
+  const int H = min(A.rows, A.ny + 2 - o0);        // output rows of this block
+  const int q = o0 - 1 + wv;
+  const bool run = wv < H + 2;                     // (fewer rows in the last strip)
+  const bool inner = wv >= 1 && wv <= H;
+  const double dtv = A.dt ? *A.dt : 0.0;
+  const T alpha = T(A.alpha[1]);
+  const T lamh = T(A.sc.lamh);
+  extern __shared__ __align__(16) char tile_smem[];
+  T* const bs = (T*)tile_smem;                     // b of row q: slot wv + 1
+  T* const cs = bs + (A.rows + 4) * 3 * R;         // to rows q - 1 and q + 1 (u, w): slot wv
+
+  T Ua[NC], Wa[NC], Ub[NC], Wb[NC], Uc[NC], Wc[NC], Va[NC], aW[NC];
+  if (run) {
+    auto load = [&](int r, T (&U)[NC], T (&W)[NC]) {
+      const unsigned off = (unsigned)(map_index(r, A.ny, A.bc_lo, A.bc_hi) * A.nx + col);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        U[c] = ld32(A.X[0], (unsigned)(c * A.plane) + off);
+        W[c] = lamh * ld32(A.X[2], (unsigned)(c * A.plane) + off);
+      }
+      if constexpr (WALLS) {
+        if (mirrored(r, A.ny, A.bc_lo, A.bc_hi)) {
+          mirror_state<Sys, 1>(true, U);
+          mirror_normal_derivative<Sys, 1>(true, W);
+        }
+        const int fs = fixed_side(r, A.ny, A.bc_lo, A.bc_hi);
+        if (fs >= 0) {
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            U[c] = T(A.gs[fs][c]);
+            W[c] = T(0);
+          }
+        }
+      }
+    };
+    // b of a row to its slot (zero at ghost rows: L is defined on interior cells)
+    auto load_b = [&](int r, int slot) {
+      const T su = T(A.sc.u * dtv), sv = T(A.sc.o * dtv), sw = T(A.sc.a * dtv);
+      const bool in = r >= 0 && r < A.ny;
+      T* d = bs + slot * 3 * R + lane;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const unsigned idx = (unsigned)(c * A.plane + (in ? r : 0) * A.nx + col);
+        d[c * kWave] = in ? su * ld32(A.b[0], idx) : T(0);
+        d[R + c * kWave] = in ? sw * ld32(A.b[2], idx) : T(0);
+        d[2 * R + c * kWave] = in ? sv * ld32(A.b[1], idx) : T(0);
+      }
+    };
+    load_b(q, wv + 1);
+    if (wv == 0) load_b(q - 1, 0);
+    if (wv == H + 1) load_b(q + 1, H + 3);
+    load(q - 1, Ua, Wa);
+    load(q, Ub, Wb);
+    load(q + 1, Uc, Wc);
+    const unsigned off = (unsigned)(map_index(q, A.ny, A.bc_lo, A.bc_hi) * A.nx + col);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      Va[c] = ld32(A.X[1], (unsigned)(c * A.plane) + off);
+      aW[c] = T(0);
+    }
+    if constexpr (WALLS) {
+      if (mirrored(q, A.ny, A.bc_lo, A.bc_hi)) mirror_state<Sys, 1>(true, Va);
+      if (fixed_side(q, A.ny, A.bc_lo, A.bc_hi) >= 0) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) Va[c] = T(0);
+      }
+    }
+    if (q >= 0 && q < A.ny) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k < A.na) {
+          const T ca = T(A.ca[k] * A.sc.vt);
+#pragma unroll
+          for (int c = 0; c < NC; ++c) aW[c] += ca * ld32(A.aw[k], (unsigned)(c * A.plane) + off);
+        }
+    }
+  }
+  lds_barrier();
+  T gU[NC], gV[NC], gW[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) gU[c] = gV[c] = gW[c] = T(0);
+  if (run) {
+    auto B = [&](int j, int f, int c) -> T { return bs[((wv + 1 + j) * 3 + f) * R + c * kWave + lane]; };
+    const auto ce = sy.cell_eig(Ub);
+    typename StateBarOf<Sys, T>::type sb{};
+    if (inner) {
+      // reverse of the row's pointwise g, theta, xi (interfaces q-3/2..q+3/2)
+      T gg[NC], gt[NC], gx[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        T l[3][4];                                 // [field][interface q+3/2 .. q-3/2]
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+          const T p2 = B(2, f, c), p1 = B(1, f, c), z = B(0, f, c), m1 = B(-1, f, c), m2 = B(-2, f, c);
+          l[f][0] = p2 - p1;
+          l[f][1] = p1 - z;
+          l[f][2] = z - m1;
+          l[f][3] = m1 - m2;
+        }
+        point_cotangents(l[0][0], l[0][1], l[0][2], l[0][3], l[1][0], l[1][1], l[1][2], l[1][3], gg[c], gt[c]);
+        gx[c] = point_cotangent_mixed(l[2][0], l[2][1], l[2][2], l[2][3]);
+      }
+      flux_vjp<1>(sy, Ub, ce.q, gg, sb, gU);
+      jac_vjp<1>(sy, Ub, ce.q, Wb, gt, sb, gU, gW);
+      jac_vjp<1>(sy, Ub, ce.q, Va, gx, sb, gU, gV);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // reverse of the row's faces and HWENO
+    T E1[NC], E2[NC], S[NC], Dd[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      E1[c] = Ub[c] - Ua[c];
+      E2[c] = Uc[c] - Ub[c];
+      S[c] = Wa[c] + Wc[c];
+      Dd[c] = Wa[c] - Wc[c];
+    }
+    T guT[NC], guB[NC], g1[NC], g2[NC], gS[NC], gD[NC];
+    {
+      T uT[NC], uB[NC], wt_[NC], wT[NC], wB[NC], gwT[NC], gwB[NC], tG[NC], tT[NC], pG[NC], pT[NC];
+      if constexpr (IFACE)
+        hweno_cell_diff_iface<1>(sy, A.pk, ce, Ua, Ub, Uc, E1, E2, S, Dd, uT, uB, wt_, wT, wB);
+      else
+        hweno_cell_diff<1>(sy, A.pk, ce, Ub, E1, E2, S, Dd, uT, uB, wt_, wT, wB);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const T g0 = B(0, 0, c), t0 = B(0, 1, c);
+        tG[c] = B(1, 0, c) - g0;
+        tT[c] = B(1, 1, c) - t0;
+        pG[c] = g0 - B(-1, 0, c);
+        pT[c] = t0 - B(-1, 1, c);
+      }
+      face_vjp<1>(sy, alpha, uT, wT, tG, tT, guT, gwT);
+      face_vjp<1>(sy, -alpha, uB, wB, pG, pT, guB, gwB);
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        face_derivs_diff_vjp(gwT[c], gwB[c], g1[c], g2[c], gS[c], gD[c]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    T tm[NC], tp[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) tm[c] = tp[c] = T(0);
+    if constexpr (IFACE && Sys::kChar)
+      hweno_cell_diff_iface_vjp<1>(sy, A.pk, ce, Ua, Ub, Uc, E1, E2, S, Dd, guT, guB, aW, g1, g2, gS, gD,
+                                   tm, gU, tp, sb);
+    else
+      hweno_cell_diff_vjp<1>(sy, A.pk, ce, E1, E2, S, Dd, guT, guB, aW, g1, g2, gS, gD, sb);
+    cell_state_vjp(sy, Ub, ce, sb, gU);
+    T* d = cs + wv * 4 * R + lane;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      gU[c] += (guT[c] + guB[c]) + (g1[c] - g2[c]);
+      d[c * kWave] = tm[c] - g1[c];
+      d[R + c * kWave] = gS[c] + gD[c];
+      d[2 * R + c * kWave] = tp[c] + g2[c];
+      d[3 * R + c * kWave] = gS[c] - gD[c];
+    }
+  }
+  lds_barrier();
+  if (inner && colok) {
+    const T* up = cs + (wv + 1) * 4 * R + lane;    // from the cell above to this row
+    const T* dn = cs + (wv - 1) * 4 * R + 2 * R + lane;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      gU[c] += up[c * kWave] + dn[c * kWave];
+      gW[c] = lamh * (gW[c] + (up[R + c * kWave] + dn[R + c * kWave]));
+    }
+    if (q >= 0 && q < A.ny) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const unsigned idx = (unsigned)(c * A.plane + q * A.nx + x);
+        st32(A.G[0], idx, gU[c]);
+        st32(A.G[1], idx, gV[c]);
+        st32(A.G[2], idx, gW[c]);
+      }
+    } else {
+      T* gp = A.ghost + (size_t)((q < 0 ? q + 2 : q - A.ny + 2) * 3 * NC) * A.nx + x;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        gp[(0 * NC + c) * A.nx] = gU[c];
+        gp[(1 * NC + c) * A.nx] = gV[c];
+        gp[(2 * NC + c) * A.nx] = gW[c];
+      }
+    }
+  }
+}
+
 // Transpose of the gravity source (euler2d-s) of one stage:
 // G_f += S^T (c dt b_f) for the fields f = u, v, w, where S(X) = g (0, 0,
 // X_0, X_2): G_f[0] += g c dt b_f[2], G_f[2] += g c dt b_f[3].
@@ -2192,7 +2402,11 @@ int balanced_rows(long col_blocks, int rows, bool known, int per_cu, int cus, do
 // rows for two) and the marcher, whose blocks share rows' warm-up over more
 // rows, is as fast. Measured (FP64 Euler, us a stage, marcher | tile): 60x60
 // 11.5 | 7.8, 60x240 11.8 | 8.1, 120x240 12.1 | 8.8, 240x240 14.0 | 10.8;
-// beyond the line 320x256 17.7 | 16.0 at best, 385x250 18.5 | 18.6.
+// beyond the line 320x256 17.7 | 16.0 at best, 385x250 18.5 | 18.6. The y-pass
+// of the adjoint follows the same rule, in both precisions (FP64 Euler, us for
+// the adjoint of a step, three y-passes in it): 64x64 105 | 56, 128x128 109 | 57,
+// 256x256 126 | 88, 320x256 131 | 93, interface basis 209 | 172, FP32 105 | 74;
+// beyond the line 384x384 161 | 151, interface basis 254 | 281, 512x512 214 | 230.
 int tile_rows(long col_blocks, int ny, int cus) {
   for (int h = 1; h <= kTileRows; ++h)
     if (col_blocks * ((ny + h - 1) / h) <= cus) return h;
@@ -2401,26 +2615,33 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
     bool walls = false;
     for (int k = 0; k < 4; ++k) walls = walls || p->bc[k] == HWENO_REFLECTIVE || p->bc[k] == HWENO_DIRICHLET;
     int nstrips = 0;
-    auto go = [&](auto kernel, auto tag) {
+    const int col_blocks = (nx + kWave - 1) / kWave;
+    auto go = [&](auto kernel, auto tile, auto tag) {
       int per_cu = 0, cus = 0;
       const bool known = occupancy<decltype(tag)::value, kWave>(kernel, &per_cu, &cus);
-      A.rows = balanced_rows((nx + kWave - 1) / kWave, ny + 4, known, per_cu, cus, 1.0, 16,
-                             kMinStripRows);
+      A.rows = known ? tile_rows(col_blocks, ny + 4, cus) : 0;
+      if (A.rows > 0) {   // no strip halos
+        const dim3 grid(col_blocks, (ny + 4 + A.rows - 1) / A.rows);
+        tile<<<grid, (A.rows + 2) * kWave, vjp_tile_lds<NC, T>(A.rows), st>>>(A, sy);
+        return;
+      }
+      A.rows = balanced_rows(col_blocks, ny + 4, known, per_cu, cus, 1.0, 16, kMinStripRows);
       nstrips = (ny + 4 + A.rows - 1) / A.rows;
-      dim3 grid((nx + kWave - 1) / kWave, nstrips);
-      kernel<<<grid, kWave, 0, st>>>(A, sy);
+      kernel<<<dim3(col_blocks, nstrips), kWave, 0, st>>>(A, sy);
     };
     if (iface) {
       if constexpr (Sys::kChar) {
         if (walls)
-          go(vjp_y_kernel<Sys, T, true, true>, std::integral_constant<int, 20>{});
+          go(vjp_y_kernel<Sys, T, true, true>, vjp_y_tile_kernel<Sys, T, true, true>,
+             std::integral_constant<int, 20>{});
         else
-          go(vjp_y_kernel<Sys, T, false, true>, std::integral_constant<int, 4>{});
+          go(vjp_y_kernel<Sys, T, false, true>, vjp_y_tile_kernel<Sys, T, false, true>,
+             std::integral_constant<int, 4>{});
       }
     } else if (walls) {
-      go(vjp_y_kernel<Sys, T, true>, std::integral_constant<int, 20>{});
+      go(vjp_y_kernel<Sys, T, true>, vjp_y_tile_kernel<Sys, T, true>, std::integral_constant<int, 20>{});
     } else {
-      go(vjp_y_kernel<Sys, T, false>, std::integral_constant<int, 4>{});
+      go(vjp_y_kernel<Sys, T, false>, vjp_y_tile_kernel<Sys, T, false>, std::integral_constant<int, 4>{});
     }
     if (check_launch() != HWENO_OK) return HWENO_EDEVICE;
     ystrip_rows = A.rows;

@@ -29,20 +29,20 @@ def test_difference_form_matches_term_by_term_form(tmp_path):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize('basis', ['cell', 'interface'])
-@pytest.mark.parametrize('n', [5, 6, 56, 57, 60, 61, 116, 117, 121])
+@pytest.mark.parametrize('n,m', [(n, 9) for n in (5, 6, 56, 57, 60, 61, 116, 117, 121)] + [(70, 800)])
 @pytest.mark.parametrize('ends', [('periodic',) * 2, ('reflective', 'transmissive'),
                                   ('transmissive', 'reflective')], ids=lambda e: e[0][:5])
-def test_adjoint_passes_agree_on_the_transposed_problem(ends, n, basis):
+def test_adjoint_passes_agree_on_the_transposed_problem(ends, n, m, basis):
     """The x-pass divides a line of n cells evenly over wavefronts of at most 60
     (or n + 4 with ghost cells) and returns what ghost cells receive within
-    the wavefront; the y-pass goes through ghost rows. The adjoint of the
-    transposed problem swaps the two. Same terms in another order: agreement to
+    the wavefront; the y-pass goes through ghost rows, on small grids with a
+    wavefront per row (all but the last size one way round), else marching. The
+    adjoint of the transposed problem swaps the two. Same terms in another order: agreement to
     1e-9 of each field's largest (rounding 1e-16, times the few 1e5 by which
     the weights' derivatives exceed the result)."""
     from paper_2411_11229_amd import hweno as H
     from paper_2411_11229_amd import workloads as WL
-    print(f'n {n} {ends} {basis}', flush=True)
-    m = 9
+    print(f'{n}x{m} {ends} {basis}', flush=True)
     w = WL.with_bc(WL.euler2d_smooth(n, seed=3200 + n, ny=m, amp=0.02), tuple(ends) + ('periodic',) * 2)
     perm = [0, 2, 1, 3]
     flip = lambda a: np.ascontiguousarray(a[perm].transpose(0, 2, 1))
