@@ -188,6 +188,25 @@ __device__ __forceinline__ StageIn stage_read(const StageArgs<T>& A) {
   return in;
 }
 
+// dt of a step that starts at t0, from its alphas, and its end time; false (dt 0)
+// if t_end is reached.
+__device__ __forceinline__ bool step_size(const StepCtl& c, double t0, double ax, double ay, double& d,
+                                          double& tn) {
+  d = c.rule == HWENO_DT_FIXED ? c.dt_fixed
+                               : c.cfl / (c.dim == 2 ? ax / c.hx + ay / c.hy : ax / c.hx);
+  tn = t0 + d;
+  if (!(t0 < c.t_end)) {
+    d = 0.0;
+    tn = t0;
+    return false;
+  }
+  if (tn >= c.t_end) {
+    d = c.t_end - t0;
+    tn = c.t_end;
+  }
+  return true;
+}
+
 // Start of a stage launch, by every wavefront: the stage's alphas, dt and time,
 // and whether the step is active. A stage 1 with time-step control computes dt
 // itself from its alphas (every block alike); the first wavefront of the first
@@ -218,18 +237,9 @@ __device__ __forceinline__ bool stage_begin(const StageArgs<T>& A, const StageIn
   if (MODE == kRhs) return true;
   if (MODE == kStage1 && c.sc) {
     if (c.dim == 1) ay = 0.0;
-    double d = c.rule == HWENO_DT_FIXED ? c.dt_fixed
-                                        : c.cfl / (c.dim == 2 ? ax / c.hx + ay / c.hy : ax / c.hx);
     const double t0 = in.t;
-    const bool active = t0 < c.t_end;
-    double tn = t0 + d;
-    if (!active) {
-      d = 0.0;
-      tn = t0;
-    } else if (tn >= c.t_end) {
-      d = c.t_end - t0;
-      tn = c.t_end;
-    }
+    double d, tn;
+    const bool active = step_size(c, t0, ax, ay, d, tn);
     if (leader) clear(kSet3);
     if (leader && !active && A.alpha_set == kSetSeed && lane < kSlots) {
       // nothing was stepped: the seed stays the next step's alphas
@@ -479,7 +489,45 @@ __device__ __forceinline__ double rk_wl(double dt) {
   else return 1.0;
 }
 
-// ------------------------------------------------------------ 1D stage kernel
+// ------------------------------------------------------------ 1D stage kernels
+// One stage on a line of 64 cells, one a lane (column col, mapped to g): from
+// the loaded U, V the new state, the modified derivative and the weighted RK
+// combination with the base Bu, Bv (stages 2-3). Halo lanes' results are void.
+template <int MODE, bool IFACE, class Sys, typename T>
+__device__ __forceinline__ void stage1d_line(const StageArgs<T>& A, const Sys& sy, int col, double ax,
+                                             double dt, T (&U)[Sys::NC], T (&V)[Sys::NC],
+                                             const T (&Bu)[Sys::NC], const T (&Bv)[Sys::NC],
+                                             T (&Un)[Sys::NC], T (&Vn)[Sys::NC], T (&Vt)[Sys::NC]) {
+  constexpr int NC = Sys::NC;
+  const bool m = mirrored(col, A.nx, A.bc[0], A.bc[1]);
+  mirror_state<Sys, 0>(m, U);
+  mirror_normal_derivative<Sys, 0>(m, V);
+  const int fs = fixed_side(col, A.nx, A.bc[0], A.bc[1]);
+  if (fs >= 0) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      U[c] = T(A.gs[fs][c]);
+      V[c] = T(0);
+    }
+  }
+  // the carried derivatives (see sweep_x)
+#pragma unroll
+  for (int c = 0; c < NC; ++c) V[c] = T(A.fk.lx) * V[c];
+  double RU[NC], RV[NC], RW[NC];
+  T W[NC], vt[NC];
+  const auto ce = sy.cell_eig(U);
+  sweep_x<2, IFACE>(sy, A.s, A.pk, ax, ce, U, V, W, RU, RV, RW, vt);
+  const double wl = rk_wl<MODE>(dt), wu = wl * A.fk.xu, wv = wl * A.fk.xv;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const double ub = MODE >= kStage2 ? (double)Bu[c] : 0.0;
+    const double vb = MODE >= kStage2 ? (double)Bv[c] : 0.0;
+    Un[c] = (T)fma(wu, RU[c], rk_base<MODE>((double)U[c], rk_x<MODE>(1.0), ub));
+    Vn[c] = (T)fma(wv, RV[c], rk_base<MODE>((double)vt[c], rk_x<MODE>(A.fk.vtx), vb));
+    Vt[c] = (T)((double)vt[c] * A.fk.vtx);
+  }
+}
+
 template <class Sys, typename T, int MODE, bool IFACE>
 __global__ __launch_bounds__(64) void stage1d_kernel(StageArgs<T> A, Sys sy) {
   constexpr int NC = Sys::NC;
@@ -488,7 +536,7 @@ __global__ __launch_bounds__(64) void stage1d_kernel(StageArgs<T> A, Sys sy) {
   const int col = blockIdx.x * kXOut - kHalo + lane;
   const int g = map_index(col, A.nx, A.bc[0], A.bc[1]);
   const bool out = lane >= kHalo && lane < kWave - kHalo && col < A.nx;
-  T U[NC], V[NC], W[NC];
+  T U[NC], V[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     U[c] = A.U[c * A.plane + g];
@@ -504,40 +552,17 @@ __global__ __launch_bounds__(64) void stage1d_kernel(StageArgs<T> A, Sys sy) {
   }
   double ax, ay, dt, tstage;
   if (!stage_begin<MODE>(A, in, blockIdx.x == 0, ax, ay, dt, tstage)) return;
-  {
-    const bool m = mirrored(col, A.nx, A.bc[0], A.bc[1]);
-    mirror_state<Sys, 0>(m, U);
-    mirror_normal_derivative<Sys, 0>(m, V);
-    const int fs = fixed_side(col, A.nx, A.bc[0], A.bc[1]);
-    if (fs >= 0) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        U[c] = T(A.gs[fs][c]);
-        V[c] = T(0);
-      }
-    }
-  }
-  // the carried derivatives (see sweep_x)
-#pragma unroll
-  for (int c = 0; c < NC; ++c) V[c] = T(A.fk.lx) * V[c];
-  double RU[NC], RV[NC], RW[NC];
-  T vt[NC];
-  const auto ce = sy.cell_eig(U);
-  sweep_x<2, IFACE>(sy, A.s, A.pk, ax, ce, U, V, W, RU, RV, RW, vt);
+  T Un[NC], Vn[NC], Vt[NC];
+  stage1d_line<MODE, IFACE>(A, sy, col, ax, dt, U, V, Bu, Bv, Un, Vn, Vt);
   double smax = 0.0;
   unsigned flag = 0;
-  const double wl = rk_wl<MODE>(dt), wu = wl * A.fk.xu, wv = wl * A.fk.xv;
   if (out) {
-    T Un[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int o = c * A.plane + col;
-      const double ub = MODE >= kStage2 ? (double)Bu[c] : 0.0;
-      const double vb = MODE >= kStage2 ? (double)Bv[c] : 0.0;
-      Un[c] = (T)fma(wu, RU[c], rk_base<MODE>((double)U[c], rk_x<MODE>(1.0), ub));
       A.Uo[o] = Un[c];
-      A.Vo[o] = (T)fma(wv, RV[c], rk_base<MODE>((double)vt[c], rk_x<MODE>(A.fk.vtx), vb));
-      if (MODE == kStage1 || MODE == kRhs) A.Vt[o] = (T)((double)vt[c] * A.fk.vtx);
+      A.Vo[o] = Vn[c];
+      if (MODE == kStage1 || MODE == kRhs) A.Vt[o] = Vt[c];
     }
     if (A.next_set >= 0) {
       double sy_;
@@ -549,6 +574,119 @@ __global__ __launch_bounds__(64) void stage1d_kernel(StageArgs<T> A, Sys sy) {
     flag = wave_or(flag);
     if (lane == 0) raise_alphas<1>(A.ctl.sc, A.nslots, A.next_set, blockIdx.x, smax, 0.0, flag);
   }
+}
+
+// Whole steps of a short line in one block ("line"): wavefront w holds the cells
+// 60 w .. 60 w + 59 (with the halo, as a block of stage1d_kernel), the state
+// stays in LDS, in two copies that the stages read and write in turn, and so do
+// the wavefronts' maxima for the alphas; one barrier a stage. The arithmetic and
+// the step control are those of the stage kernels. A launch of those is bound by
+// latency and the launch itself, not by its work; here a stage costs its
+// arithmetic, the wavefronts of one CU sharing it, and a barrier. FP64 only (see
+// rounded()). Measured at the rule (line_fits).
+constexpr int kLineSteps = 64;                     // most steps of a launch
+constexpr int line_waves(bool iface) { return iface ? 8 : 16; }
+template <int NC, typename T>
+constexpr size_t line_lds(int nx) {
+  return (size_t)4 * NC * nx * sizeof(T) + 2 * line_waves(false) * sizeof(double);
+}
+template <class Sys, typename T, bool IFACE>
+__global__ __launch_bounds__(line_waves(IFACE) * kWave) void steps1d_kernel(StageArgs<T> A, Sys sy,
+                                                                           int nsteps) {
+  constexpr int NC = Sys::NC;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int nw = blockDim.x / kWave;
+  const StepCtl& ctl = A.ctl;
+  const int col = wv * kXOut - kHalo + lane;
+  const int g = map_index(col, A.nx, A.bc[0], A.bc[1]);
+  const bool out = lane >= kHalo && lane < kWave - kHalo && col < A.nx;
+  const bool first = threadIdx.x == 0;
+  extern __shared__ __align__(16) char line_smem[];
+  double* const peak = (double*)line_smem;         // [copy][wavefront]
+  T* const state = (T*)(peak + 2 * line_waves(false));   // [copy][u, v][NC][nx]
+  auto at = [&](int p, int f, int c, int i) -> T& { return state[((p * 2 + f) * NC + c) * A.nx + i]; };
+  double smax = 0.0;
+  unsigned flag = 0;
+  if (out) {
+    T u[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      u[c] = A.Uo[c * A.plane + col];
+      at(0, 0, c, col) = u[c];
+      at(0, 1, c, col) = A.Vo[c * A.plane + col];
+    }
+    double sy_;
+    flag = sy.speeds(u, smax, sy_);
+  }
+  double t = *ctl.t;
+  int p = 0;                                       // the copy that holds the state
+  smax = wave_max(smax);
+  if (lane == 0) peak[wv] = smax;
+  __syncthreads();
+  auto alpha = [&]() { return wave_max(lane < nw ? peak[p * line_waves(false) + lane] : 0.0); };
+  T Bu[NC], Bv[NC];                                // RK base
+#pragma unroll
+  for (int c = 0; c < NC; ++c) Bu[c] = Bv[c] = T(0);
+  auto stage = [&](auto mode, double ax, double dt) {
+    constexpr int MODE = decltype(mode)::value;
+    T U[NC], V[NC], Un[NC], Vn[NC], Vt[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      U[c] = at(p, 0, c, g);
+      V[c] = at(p, 1, c, g);
+      if (MODE == kStage1) Bu[c] = U[c];
+    }
+    stage1d_line<MODE, IFACE>(A, sy, col, ax, dt, U, V, Bu, Bv, Un, Vn, Vt);
+    p ^= 1;
+    double sx = 0.0;
+    if (out) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        at(p, 0, c, col) = Un[c];
+        at(p, 1, c, col) = Vn[c];
+        if (MODE == kStage1) Bv[c] = Vt[c];
+      }
+      double sy_;
+      flag |= sy.speeds(Un, sx, sy_);
+    }
+    sx = wave_max(sx);
+    if (lane == 0) peak[p * line_waves(false) + wv] = sx;
+    __syncthreads();
+  };
+  for (int k = 0; k < nsteps; ++k) {
+    double ax = alpha(), tn;
+    double* rec = A.alpha_rec ? A.alpha_rec + 6 * k : nullptr;
+    auto record = [&](int j) {
+      if (rec && first) {
+        rec[2 * j] = ax;
+        rec[2 * j + 1] = 0.0;
+      }
+    };
+    double dt;
+    const bool active = step_size(ctl, t, ax, 0.0, dt, tn);
+    if (first && ctl.dt_used) ctl.dt_used[k] = dt;
+    record(0);
+    if (!active) continue;                         // (alike in every wavefront)
+    stage(std::integral_constant<int, kStage1>{}, ax, dt);
+    ax = alpha();
+    record(1);
+    stage(std::integral_constant<int, kStage2>{}, ax, dt);
+    ax = alpha();
+    record(2);
+    stage(std::integral_constant<int, kStage3>{}, ax, dt);
+    t = tn;
+  }
+  if (out) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      A.Uo[c * A.plane + col] = at(p, 0, c, col);
+      A.Vo[c * A.plane + col] = at(p, 1, c, col);
+    }
+  }
+  flag = wave_or(flag);
+  if (lane == 0 && flag) atomicOr(&ctl.sc->flags, flag);
+  if (first) *ctl.t = t;
 }
 
 // ------------------------------------------------------------ 2D stage kernel
@@ -2764,7 +2902,32 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
   return HWENO_OK;
 }
 
-// Time-stepping loop of hweno_step(s) ((fully-hweno), (2Dfully-hweno)): one
+// Whether a 1D problem's steps run in one block: as long as a block holds the
+// line (16 wavefronts, with the interface basis 8, which its registers allow).
+// There one CU's share of the arithmetic still takes less than a launch per
+// stage. Measured (us for 32 steps, launches | one block): Burgers N = 60 351 |
+// 60, 480 392 | 90, 960 386 | 152; Euler N = 60 431 | 144, 480 479 | 236, 960
+// 476 | 422; interface basis N = 60 499 | 214, 480 548 | 376. One step alone:
+// 19-24 | 11-18.
+template <class Sys>
+bool line_fits(const hweno_problem* p) {
+  const bool iface = Sys::kChar && p->char_basis == HWENO_BASIS_INTERFACE;
+  return p->nx <= line_waves(iface) * kXOut;
+}
+template <class Sys, typename T>
+void launch_line(const StageArgs<T>& A, const Sys& sy, int nsteps, hipStream_t st) {
+  const int waves = (A.nx + kXOut - 1) / kXOut;
+  auto go = [&](auto kernel) {
+    kernel<<<1, waves * kWave, line_lds<Sys::NC, T>(A.nx), st>>>(A, sy, nsteps);
+  };
+  if constexpr (Sys::kChar) {
+    if (A.iface) return go(steps1d_kernel<Sys, T, true>);
+  }
+  go(steps1d_kernel<Sys, T, false>);
+}
+
+// Time-stepping loop of hweno_step(s) ((fully-hweno), (2Dfully-hweno)). Short 1D
+// lines (line_fits): one launch for up to kLineSteps steps. Else one
 // seeding pass (the maxima of the spectral radii of the initial state, into the
 // accumulators of the stage-1 alphas), then three stage launches per step. Stage 1 computes the
 // step's dt from its alphas, stage 3 reduces the next step's stage-1 alphas
@@ -2797,10 +2960,6 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
     auto F = [&](char* b, int f) { return (T*)(b + (size_t)f * g.nc * P * sizeof(T)); };
     // (a 1D stage has a block per kXOut cells; in 2D a small grid has more)
     const int nslots = DIM == 1 && (p->nx + kXOut - 1) / kXOut <= kOneSlotBlocks ? 1 : kSlots;
-    int nb;
-    hweno_status s2 =
-        launch_speed_partial<Sys, T, DIM>(p, (const T*)u, sy, nullptr, wl.sc, nslots, stream, &nb);
-    if (s2 != HWENO_OK) return s2;
     StageArgs<T> A = base_args<T>(p);
     A.dt = &wl.sc->dt;
     A.active = &wl.sc->active;
@@ -2820,6 +2979,24 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
       A.ctl.hx = p->dx;
       A.ctl.hy = DIM == 2 ? p->dy : 1.0;
     }
+    if constexpr (DIM == 1 && sizeof(T) == 8) {
+      if (!stages && !events && line_fits<Sys>(p)) {
+        A.Uo = (T*)u;
+        A.Vo = (T*)v;
+        for (int k = 0; k < nsteps; k += kLineSteps) {
+          A.alpha_rec = alpha_rec ? alpha_rec + 6 * k : nullptr;
+          A.ctl.dt_used = dt_used ? dt_used + k : nullptr;
+          const int n = nsteps - k < kLineSteps ? nsteps - k : kLineSteps;
+          launch_line<Sys, T>(A, sy, n, stream);
+          if (check_launch() != HWENO_OK) return HWENO_EDEVICE;
+        }
+        return HWENO_OK;
+      }
+    }
+    int nb;
+    hweno_status s2 =
+        launch_speed_partial<Sys, T, DIM>(p, (const T*)u, sy, nullptr, wl.sc, nslots, stream, &nb);
+    if (s2 != HWENO_OK) return s2;
     for (int k = 0; k < nsteps; ++k) {
       hipEvent_t* ev = events ? events + 4 * k : nullptr;
       auto mark = [&](int j) -> bool { return !ev || hipEventRecord(ev[j], stream) == hipSuccess; };
