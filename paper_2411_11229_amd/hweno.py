@@ -176,7 +176,9 @@ def _ptr(t):
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    # the raw handle: torch.cuda.current_stream builds a Stream object (1.5 us)
+    index = device.index if device.index is not None else torch.cuda.current_device()
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(index))
 
 
 class Solver:
@@ -188,6 +190,7 @@ class Solver:
         self.cp = _CProblem()
         self.cp = prob.c()
         self.device = torch.device(device)
+        self._shape, self._dtype = torch.Size(prob.shape), prob.dtype
         nbytes = ctypes.c_size_t()
         _check(self.lib.hweno_workspace_bytes(ctypes.byref(self.cp), ctypes.byref(nbytes)),
                'hweno_workspace_bytes')
@@ -201,11 +204,11 @@ class Solver:
             if allow_none:
                 return None
             raise ValueError(f'{name} is required')
-        if not isinstance(t, torch.Tensor) or t.device.type != 'cuda':
+        if not isinstance(t, torch.Tensor) or not t.is_cuda:
             raise ValueError(f'{name} must be a HIP-device torch tensor')
-        if t.dtype != self.prob.dtype:
+        if t.dtype != self._dtype:
             raise ValueError(f'{name}: dtype {t.dtype} != {self.prob.dtype}')
-        if tuple(t.shape) != self.prob.shape:
+        if t.shape != self._shape:
             raise ValueError(f'{name}: shape {tuple(t.shape)} != {self.prob.shape}')
         if not t.is_contiguous():
             raise ValueError(f'{name} must be contiguous')
