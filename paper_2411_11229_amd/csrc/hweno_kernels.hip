@@ -1139,8 +1139,10 @@ __device__ __forceinline__ void lds_barrier() {
 // bound by latency: the start, one row's loads (2.6 us) and a row's serial
 // arithmetic (3.5 us). FP64 only (in FP32 a row's bits depend on the loop it is
 // compiled into, see rounded()). Measured times at the rule (tile_rows).
-constexpr int kTileRows = 6;                       // most output rows of a block
-constexpr int kTileThreads = (kTileRows + 2) * kWave;
+// MOST: the most output rows of a block, up to kTileFew with two wavefronts a
+// SIMD, beyond (and at most kTileRows, which a CU's LDS holds) with three, whose
+// smaller share of the registers costs the shorter blocks 0.8-1.0 us a stage.
+constexpr int kTileFew = 6, kTileRows = 8;
 // LDS of a block: per row y0-2 .. y0+H+1 the pointwise g, theta, xi; per row
 // y0-1 .. y0+H the LF sums of its top and bottom face for g and theta
 template <int NC, typename T>
@@ -1148,8 +1150,8 @@ constexpr size_t tile_lds(int H) {
   return ((size_t)(H + 4) * 3 + (size_t)(H + 2) * 4) * NC * kWave * sizeof(T);
 }
 
-template <class Sys, typename T, int MODE, int VAR>
-__global__ __launch_bounds__(kTileThreads, 2) void stage2d_tile_kernel(StageArgs<T> A, Sys sy) {
+template <class Sys, typename T, int MODE, int VAR, int MOST>
+__global__ __launch_bounds__((MOST + 2) * kWave, MOST > kTileFew ? 3 : 2) void stage2d_tile_kernel(StageArgs<T> A, Sys sy) {
   constexpr bool WALLS = (VAR & kVarWalls) != 0;
   constexpr bool IFACE = (VAR & kVarIface) != 0;
   constexpr bool SOURCE = (VAR & kVarSource) != 0 && Sys::kChar && Sys::NC == 4;
@@ -1341,7 +1343,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void stage2d_tile_kernel(StageArgs
     smy = wave_max(smy);
     flag = wave_or(flag);
     if (lane == 0)
-      raise_alphas<2>(A.ctl.sc, A.nslots, A.next_set, (blockIdx.x + gridDim.x * blockIdx.y) * kTileRows + wv,
+      raise_alphas<2>(A.ctl.sc, A.nslots, A.next_set, (blockIdx.x + gridDim.x * blockIdx.y) * MOST + wv,
                       smx, smy, flag);
   }
 }
@@ -2055,12 +2057,14 @@ __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
 // sums are complete within the block: no halo terms. Bound by latency (the start,
 // the loads, one row's serial arithmetic) in place of the marcher's H + 4 rows
 // one after the other; measured at the rule (tile_rows).
+constexpr int kVjpTileRows = 6;
+constexpr int kVjpTileThreads = (kVjpTileRows + 2) * kWave;
 template <int NC, typename T>
 constexpr size_t vjp_tile_lds(int H) {
   return ((size_t)(H + 4) * 3 + (size_t)(H + 2) * 4) * NC * kWave * sizeof(T);
 }
 template <class Sys, typename T, bool WALLS, bool IFACE = false>
-__global__ __launch_bounds__(kTileThreads, 2) void vjp_y_tile_kernel(VjpYArgs<T> A, Sys sy) {
+__global__ __launch_bounds__(kVjpTileThreads, 2) void vjp_y_tile_kernel(VjpYArgs<T> A, Sys sy) {
   constexpr int NC = Sys::NC;
   constexpr int R = NC * kWave;                    // values of one field of one row
   const int lane = threadIdx.x & (kWave - 1);
@@ -2563,28 +2567,30 @@ int balanced_rows(long col_blocks, int rows, bool known, int per_cu, int cus, do
   return best;
 }
 
-// Rows of a block of the tile kernel, 0 for the marcher: the fewest with which
-// the blocks are at most one a CU, so that every row of the grid is under way
-// at once. A stage then takes about the time of one row; with more blocks a
-// second round follows (a block's LDS leaves room for one a CU, at one or two
-// rows for two) and the marcher, whose blocks share rows' warm-up over more
-// rows, is as fast. Measured (FP64 Euler, us a stage, marcher | tile): 60x60
-// 11.5 | 7.8, 60x240 11.8 | 8.1, 120x240 12.1 | 8.8, 240x240 14.0 | 10.8;
-// beyond the line 320x256 17.7 | 16.0 at best, 385x250 18.5 | 18.6. The y-pass
-// of the adjoint follows the same rule, in both precisions (FP64 Euler, us for
+// Rows of a block of the tile kernel, 0 for the marcher: the fewest (of at most
+// `most`) with which the blocks are at most one a CU, so that every row of the
+// grid is under way at once. A stage then takes about the time of one row; with
+// more blocks a second round follows (a block's LDS leaves room for one a CU, at
+// one or two rows for two) and the marcher, whose blocks share rows' warm-up over
+// more rows, is as fast. Measured (FP64 Euler, us a stage, marcher | tile): 60x60
+// 11.2 | 7.6, 60x240 11.5 | 7.9, 240x240 13.7 | 11.0, 256x256 17.4 | 12.5, 320x256
+// 17.6 | 14.6, 385x250 18.3 | 15.2, 480x256 19.0 | 16.9; in two rounds 385x250 |
+// 18.6. The y-pass of the adjoint follows the same rule, in both precisions (FP64 Euler, us for
 // the adjoint of a step, three y-passes in it): 64x64 105 | 56, 128x128 109 | 57,
 // 256x256 126 | 88, 320x256 131 | 93, interface basis 209 | 172, FP32 105 | 74;
 // beyond the line 384x384 161 | 151, interface basis 254 | 281, 512x512 214 | 230.
-int tile_rows(long col_blocks, int ny, int cus) {
-  for (int h = 1; h <= kTileRows; ++h)
+int tile_rows(long col_blocks, int ny, int cus, int most) {
+  for (int h = 1; h <= most; ++h)
     if (col_blocks * ((ny + h - 1) / h) <= cus) return h;
   return 0;
 }
 
 // The tile kernel of a stage (FP64; nullptr for FP32, which has none).
 template <class Sys, typename T, int MODE, int VAR>
-auto tile_kernel() {
-  if constexpr (sizeof(T) == 8) return stage2d_tile_kernel<Sys, T, MODE, VAR>;
+auto tile_kernel(int rows) {
+  if constexpr (sizeof(T) == 8)
+    return rows > kTileFew ? stage2d_tile_kernel<Sys, T, MODE, VAR, kTileRows>
+                           : stage2d_tile_kernel<Sys, T, MODE, VAR, kTileFew>;
   else return nullptr;
 }
 
@@ -2617,10 +2623,10 @@ hweno_status launch_stage(int mode, const StageArgs<T>& A0, const Sys& sy, hipSt
       const bool known = occupancy<decltype(tag)::value, kWave>(kernel, &per_cu, &cus);
       const int forced = g_strip_rows.load(std::memory_order_relaxed);
       if constexpr (sizeof(T) == 8) {
-        A.rows = known && forced <= 0 ? tile_rows(col_blocks, A.ny, cus) : 0;
+        A.rows = known && forced <= 0 ? tile_rows(col_blocks, A.ny, cus, kTileRows) : 0;
         if (A.rows > 0) {
           const dim3 grid(col_blocks, (A.ny + A.rows - 1) / A.rows);
-          tile<<<grid, (A.rows + 2) * kWave, tile_lds<Sys::NC, T>(A.rows), st>>>(A, sy);
+          tile(A.rows)<<<grid, (A.rows + 2) * kWave, tile_lds<Sys::NC, T>(A.rows), st>>>(A, sy);
           return;
         }
       }
@@ -2634,10 +2640,10 @@ hweno_status launch_stage(int mode, const StageArgs<T>& A0, const Sys& sy, hipSt
       constexpr int V = decltype(var)::value;
       constexpr int kT = 16 * V;   // separate occupancy cache entries
       switch (mode) {
-        case kRhs: go(stage2d_kernel<Sys, T, kRhs, V>, tile_kernel<Sys, T, kRhs, V>(), std::integral_constant<int, kRhs + kT>{}); break;
-        case kStage1: go(stage2d_kernel<Sys, T, kStage1, V>, tile_kernel<Sys, T, kStage1, V>(), std::integral_constant<int, kStage1 + kT>{}); break;
-        case kStage2: go(stage2d_kernel<Sys, T, kStage2, V>, tile_kernel<Sys, T, kStage2, V>(), std::integral_constant<int, kStage2 + kT>{}); break;
-        default: go(stage2d_kernel<Sys, T, kStage3, V>, tile_kernel<Sys, T, kStage3, V>(), std::integral_constant<int, kStage3 + kT>{}); break;
+        case kRhs: go(stage2d_kernel<Sys, T, kRhs, V>, [](int h) { return tile_kernel<Sys, T, kRhs, V>(h); }, std::integral_constant<int, kRhs + kT>{}); break;
+        case kStage1: go(stage2d_kernel<Sys, T, kStage1, V>, [](int h) { return tile_kernel<Sys, T, kStage1, V>(h); }, std::integral_constant<int, kStage1 + kT>{}); break;
+        case kStage2: go(stage2d_kernel<Sys, T, kStage2, V>, [](int h) { return tile_kernel<Sys, T, kStage2, V>(h); }, std::integral_constant<int, kStage2 + kT>{}); break;
+        default: go(stage2d_kernel<Sys, T, kStage3, V>, [](int h) { return tile_kernel<Sys, T, kStage3, V>(h); }, std::integral_constant<int, kStage3 + kT>{}); break;
       }
     };
     bool walls = false;
@@ -2783,7 +2789,7 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
     auto go = [&](auto kernel, auto tile, auto tag) {
       int per_cu = 0, cus = 0;
       const bool known = occupancy<decltype(tag)::value, kWave>(kernel, &per_cu, &cus);
-      A.rows = known ? tile_rows(col_blocks, ny + 4, cus) : 0;
+      A.rows = known ? tile_rows(col_blocks, ny + 4, cus, kVjpTileRows) : 0;
       if (A.rows > 0) {   // no strip halos
         const dim3 grid(col_blocks, (ny + 4 + A.rows - 1) / A.rows);
         tile<<<grid, (A.rows + 2) * kWave, vjp_tile_lds<NC, T>(A.rows), st>>>(A, sy);

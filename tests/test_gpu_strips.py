@@ -32,7 +32,8 @@ def _workload(kind, nx, ny):
 
 
 CASES = [('quadrants', 61, 37), ('quadrants', 121, 250), ('quadrants', 6, 5),
-         ('quadrants', 300, 301), ('quadrants', 300, 307), ('interface', 60, 41), ('walls', 59, 23), ('rayleigh-taylor', 40, None), ('double-mach', 34, None),
+         ('quadrants', 300, 301), ('quadrants', 300, 307), ('interface', 384, 251), ('walls', 384, 257),
+         ('quadrants', 300, 408), ('quadrants', 300, 409), ('interface', 60, 41), ('walls', 59, 23), ('rayleigh-taylor', 40, None), ('double-mach', 34, None),
          ('burgers', 70, None)]
 
 
