@@ -2,6 +2,10 @@
 // hweno_device.h, written by hand. Each *_vjp recomputes what it needs of the
 // forward pass and ADDS its cotangent contributions to the output arrays.
 //
+// These are the direct forms, term by term. The kernels run the difference forms
+// of hweno_adjoint_diff.h (and from here the fluxes of the scalar laws); the
+// host checks hold those against these, and these against finite differences.
+//
 // Conventions: alpha and dt are constants (not differentiated); the
 // derivative of |x| at x = 0 is taken as 0 (the kinks of |beta0 - beta_k|).
 #pragma once
