@@ -59,7 +59,7 @@ struct StepScalars {
 // (by stage 2), kSetNext the next step's stage-1 alphas, i.e. those of the
 // step's result (by stage 3), kSetSeed the stage-1 alphas of a call's first step
 // (by the pass over its initial state). Between calls kSet2 and kSetSeed are
-// zero.
+// zero, also after a call that returned an error (alpha_clear_kernel).
 constexpr int kSlots = 32, kSets = 4, kOneSlotBlocks = 64;
 enum AlphaSet { kSet2 = 0, kSet3 = 1, kSetNext = 2, kSetSeed = 3 };
 constexpr size_t kSlotOffset = 2048;   // from the scalars, in bytes
@@ -1428,11 +1428,17 @@ __global__ __launch_bounds__(256) void speed_kernel(const T* U, int plane, Sys s
   }
 }
 
-__global__ __launch_bounds__(kWave) void ws_init_kernel(StepScalars* sc) {
+__device__ __forceinline__ void clear_alphas(StepScalars* sc) {
   const int lane = threadIdx.x;
   if (lane < kSlots)
     for (int k = 0; k < kSets; ++k) alpha_slots(sc)->v[lane][k][0] = alpha_slots(sc)->v[lane][k][1] = 0ull;
-  if (lane != 0) return;
+}
+// After a step that returns an error between its launches: the maxima that its
+// later stages would have cleared (the sticky flags stay).
+__global__ __launch_bounds__(kWave) void alpha_clear_kernel(StepScalars* sc) { clear_alphas(sc); }
+__global__ __launch_bounds__(kWave) void ws_init_kernel(StepScalars* sc) {
+  clear_alphas(sc);
+  if (threadIdx.x != 0) return;
   sc->dt = sc->t0 = sc->tnew = 0.0;
   sc->active = 0;
   sc->flags = 0u;
@@ -3011,15 +3017,21 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
         return HWENO_OK;
       }
     }
+    // an error between the launches: what they raised must not reach a later call
+    auto failed = [&](hweno_status s) {
+      alpha_clear_kernel<<<1, kWave, 0, stream>>>(wl.sc);
+      (void)hipGetLastError();
+      return s;
+    };
     hweno_status s2 = launch_speed<Sys, T, DIM>(p, (const T*)u, sy, wl.sc, nslots, nullptr, stream);
-    if (s2 != HWENO_OK) return s2;
+    if (s2 != HWENO_OK) return failed(s2);
     for (int k = 0; k < nsteps; ++k) {
       hipEvent_t* ev = events ? events + 4 * k : nullptr;
       auto mark = [&](int j) -> bool { return !ev || hipEventRecord(ev[j], stream) == hipSuccess; };
       double* rec = alpha_rec ? alpha_rec + 6 * k : nullptr;
       A.ctl.dt_used = dt_used ? dt_used + k : nullptr;
       // stage 1: X^n -> X^(1), V~^n, W~^n; computes dt
-      if (!mark(0)) return HWENO_EDEVICE;
+      if (!mark(0)) return failed(HWENO_EDEVICE);
       A.U = (const T*)u; A.V = (const T*)v; A.W = (const T*)w;
       A.Ub = nullptr; A.Vb = nullptr; A.Wb = nullptr;
       A.Uo = F(x1, 0); A.Vo = F(x1, 1); A.Wo = DIM == 2 ? F(x1, 2) : nullptr;
@@ -3028,8 +3040,8 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
       A.next_set = kSet2;
       A.alpha_rec = rec;
       A.tc = 0.0;
-      if ((s2 = launch_stage<Sys, T, DIM>(kStage1, A, sy, stream)) != HWENO_OK) return s2;
-      if (!mark(1)) return HWENO_EDEVICE;
+      if ((s2 = launch_stage<Sys, T, DIM>(kStage1, A, sy, stream)) != HWENO_OK) return failed(s2);
+      if (!mark(1)) return failed(HWENO_EDEVICE);
       // stage 2: X^(1) -> X^(2) with base (U^n, V~^n, W~^n)
       A.U = F(x1, 0); A.V = F(x1, 1); A.W = DIM == 2 ? F(x1, 2) : nullptr;
       A.Ub = (const T*)u; A.Vb = Vt; A.Wb = Wt;
@@ -3039,8 +3051,8 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
       A.next_set = kSet3;
       A.alpha_rec = rec ? rec + 2 : nullptr;
       A.tc = 1.0;
-      if ((s2 = launch_stage<Sys, T, DIM>(kStage2, A, sy, stream)) != HWENO_OK) return s2;
-      if (!mark(2)) return HWENO_EDEVICE;
+      if ((s2 = launch_stage<Sys, T, DIM>(kStage2, A, sy, stream)) != HWENO_OK) return failed(s2);
+      if (!mark(2)) return failed(HWENO_EDEVICE);
       // stage 3: X^(2) -> X^{n+1}, in place on (u, v, w); the result's alphas
       // are the next step's stage-1 alphas
       A.U = F(x2, 0); A.V = F(x2, 1); A.W = DIM == 2 ? F(x2, 2) : nullptr;
@@ -3049,8 +3061,8 @@ hweno_status run_steps(const hweno_problem* p, void* u, void* v, void* w, int32_
       A.next_set = kSetNext;
       A.alpha_rec = rec ? rec + 4 : nullptr;
       A.tc = 0.5;
-      if ((s2 = launch_stage<Sys, T, DIM>(kStage3, A, sy, stream)) != HWENO_OK) return s2;
-      if (!mark(3)) return HWENO_EDEVICE;
+      if ((s2 = launch_stage<Sys, T, DIM>(kStage3, A, sy, stream)) != HWENO_OK) return failed(s2);
+      if (!mark(3)) return failed(HWENO_EDEVICE);
     }
     return HWENO_OK;
   });
