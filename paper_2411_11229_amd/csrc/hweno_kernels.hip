@@ -45,7 +45,6 @@ struct StepScalars {
   double tnew;                    // its end time (t0 + dt, or t_end when clipped)
   int active;
   unsigned flags;
-  unsigned ticket;                // blocks of a speed_kernel launch that are done (0 between)
 };
 
 // Accumulators of the Lax-Friedrichs alphas, behind the scalars: kSlots slots,
@@ -68,6 +67,17 @@ struct AlphaSlots {
 };
 __host__ __device__ inline AlphaSlots* alpha_slots(StepScalars* sc) {
   return (AlphaSlots*)((char*)sc + kSlotOffset);
+}
+// Behind the accumulators: the blocks of a speed_kernel launch that are done, per
+// slot, each count in a line of its own, and the slots whose blocks all are. Zero
+// between launches.
+struct SpeedTickets {
+  unsigned slot[kSlots][16];
+  unsigned slots;
+};
+constexpr size_t kTicketOffset = kSlotOffset + sizeof(AlphaSlots);
+__host__ __device__ inline SpeedTickets* speed_tickets(StepScalars* sc) {
+  return (SpeedTickets*)((char*)sc + kTicketOffset);
 }
 
 // Time-step control of a stage-1 launch that computes dt itself (flux-LF): from
@@ -145,8 +155,8 @@ __device__ __forceinline__ unsigned wave_or(unsigned v) {
 }
 // Atomic max of non-negative doubles through their bit patterns (ordered
 // like unsigned integers); order-independent, hence deterministic.
-__device__ __forceinline__ void atomic_max_pos(unsigned long long* p, double v) {
-  atomicMax(p, (unsigned long long)__double_as_longlong(v));
+__device__ __forceinline__ unsigned long long atomic_max_pos(unsigned long long* p, double v) {
+  return atomicMax(p, (unsigned long long)__double_as_longlong(v));
 }
 // One lane adds its block's maxima and state flags to the accumulators.
 template <int DIM>
@@ -1372,11 +1382,16 @@ __global__ __launch_bounds__((MOST + 2) * kWave, MOST > kTileFew ? 3 : 2) void s
 // -------------------------------------------- wave-speed reduction (flux-LF)
 // The maxima of the spectral radius over interior cells, in x and y, into the
 // accumulators kSetSeed, for a run's first step (alpha null); also raises the
-// state flags. With `alpha` the maxima are the result: the block that raises its
-// own last takes them from the accumulators (leaving zeros) and writes them. The
-// blocks' tickets order that: a block takes one after its maxima are visible on
-// the whole device, and nobody waits. (A second launch for the maxima of the
-// blocks' maxima: 2.9 us and 4 us of the host's time.)
+// state flags. With `alpha` the maxima are the result: the block that is done
+// last takes them from the accumulators (leaving zeros) and writes them; nobody
+// waits. A block counts itself as done once its atomic maxima have returned, that
+// is once they stand where every block's atomics meet; the maxima and the counts
+// are only ever accessed by such atomics, so that no cache has to be written back
+// or invalidated. The blocks are counted per slot, then the slots. Measured (FP64
+// Euler, us a launch, this | with a device-wide fence a block, one count | two
+// launches): 128^2 4.3 | 4.3 | 5.3, 385x250 4.4 | 9.5 | 5.5, 512^2 5.0 | 22.0 | 5.3,
+// 1000x777 6.1 | 22.5 | 6.0, 2000^2 21.2 | 39.7 | 21.4; the second launch also
+// costs 4 us of the host's time.
 template <class Sys, typename T, int DIM>
 __global__ __launch_bounds__(256) void speed_kernel(const T* U, int plane, Sys sy, StepScalars* sc,
                                                     int nslots, double* alpha) {
@@ -1405,26 +1420,36 @@ __global__ __launch_bounds__(256) void speed_kernel(const T* U, int plane, Sys s
   if (lane == 0) {
     const int nw = blockDim.x / kWave;
     for (int k = 1; k < nw; ++k) { mx = fmax(mx, sx[k]); my = fmax(my, sy_[k]); flag |= sf[k]; }
-    raise_alphas<DIM>(sc, nslots, kSetSeed, blockIdx.x, mx, my, flag);
-    if (alpha) {
-      __threadfence();
-      last = atomicAdd(&sc->ticket, 1u) == gridDim.x - 1;
-      if (last) __threadfence();
+    if (!alpha) {
+      raise_alphas<DIM>(sc, nslots, kSetSeed, blockIdx.x, mx, my, flag);
+    } else {
+      const unsigned slot = blockIdx.x % kSlots, nb = gridDim.x;
+      unsigned long long* p = alpha_slots(sc)->v[slot][kSetSeed];
+      SpeedTickets* done = speed_tickets(sc);
+      const unsigned long long ox = atomic_max_pos(p, mx), oy = DIM == 2 ? atomic_max_pos(p + 1, my) : 0ull;
+      if (flag) atomicOr(&sc->flags, flag);
+      // the old values are here: both maxima stand (nothing moves above this)
+      asm volatile("s_waitcnt vmcnt(0)" ::"v"((unsigned)ox), "v"((unsigned)oy) : "memory");
+      if (atomicAdd(&done->slot[slot][0], 1u) == (nb - slot + kSlots - 1) / kSlots - 1) {
+        asm volatile("" ::: "memory");
+        last = atomicAdd(&done->slots, 1u) == (nb < kSlots ? nb : kSlots) - 1;
+      }
     }
   }
   if (!__any(last)) return;
   double x = 0.0, y = 0.0;
-  if (lane < nslots) {
+  if (lane < kSlots) {
     unsigned long long* p = alpha_slots(sc)->v[lane][kSetSeed];
     x = __longlong_as_double((long long)atomicExch(p, 0ull));
     if (DIM == 2) y = __longlong_as_double((long long)atomicExch(p + 1, 0ull));
+    atomicExch(&speed_tickets(sc)->slot[lane][0], 0u);
   }
   x = wave_max(x);
   y = wave_max(y);
   if (lane == 0) {
     alpha[0] = x;
     alpha[1] = y;
-    atomicExch(&sc->ticket, 0u);
+    atomicExch(&speed_tickets(sc)->slots, 0u);
   }
 }
 
@@ -1438,11 +1463,12 @@ __device__ __forceinline__ void clear_alphas(StepScalars* sc) {
 __global__ __launch_bounds__(kWave) void alpha_clear_kernel(StepScalars* sc) { clear_alphas(sc); }
 __global__ __launch_bounds__(kWave) void ws_init_kernel(StepScalars* sc) {
   clear_alphas(sc);
+  if (threadIdx.x < kSlots) speed_tickets(sc)->slot[threadIdx.x][0] = 0u;
   if (threadIdx.x != 0) return;
   sc->dt = sc->t0 = sc->tnew = 0.0;
   sc->active = 0;
   sc->flags = 0u;
-  sc->ticket = 0u;
+  speed_tickets(sc)->slots = 0u;
 }
 
 // ================================================================ adjoint
@@ -2328,10 +2354,10 @@ using namespace hweno;
 
 namespace {
 
-// StepScalars and AlphaSlots. (Larger than they need: with the stage states this
+// StepScalars, AlphaSlots and SpeedTickets. (Larger than they need: with the stage states this
 // decides which problems hweno_step_noalloc's scratch holds.)
 constexpr size_t kScalarBytes = 20480;
-static_assert(sizeof(StepScalars) <= kSlotOffset && kSlotOffset + sizeof(AlphaSlots) <= kScalarBytes);
+static_assert(sizeof(StepScalars) <= kSlotOffset && kTicketOffset + sizeof(SpeedTickets) <= kScalarBytes);
 constexpr int kSpeedBlocks = 1024;
 constexpr int kRowsPerBlock = 32;
 
