@@ -176,7 +176,10 @@ def _ptr(t):
 
 
 def _stream(device):
-    # the raw handle: torch.cuda.current_stream builds a Stream object (1.5 us)
+    # the raw handle: torch.cuda.current_stream builds a Stream object (1.5 us),
+    # and would refuse other devices itself
+    if device.type != 'cuda':
+        raise ValueError(f'{device} is not a HIP device')
     index = device.index if device.index is not None else torch.cuda.current_device()
     return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(index))
 
