@@ -194,6 +194,7 @@ class Solver:
         self.cp = prob.c()
         self.device = torch.device(device)
         self._shape, self._dtype = torch.Size(prob.shape), prob.dtype
+        self._made_for = (prob.dim, prob.nx, prob.ny, prob.system, prob.precision)
         nbytes = ctypes.c_size_t()
         _check(self.lib.hweno_workspace_bytes(ctypes.byref(self.cp), ctypes.byref(nbytes)),
                'hweno_workspace_bytes')
@@ -202,6 +203,14 @@ class Solver:
                                              _stream(self.device)), 'hweno_workspace_init')
 
     # ------------------------------------------------------------ checks
+    def _two(self):
+        """Whether the problem is 2D. Every entry point asks first: the arrays are
+        checked against, and allocated for, the problem the library was given."""
+        p = self.prob
+        if (p.dim, p.nx, p.ny, p.system, p.precision) != self._made_for:
+            raise ValueError('the problem was changed after its solver was made')
+        return p.dim == 2
+
     def _state(self, t, name, allow_none=False):
         if t is None:
             if allow_none:
@@ -228,6 +237,7 @@ class Solver:
 
     # ------------------------------------------------------------ entry points
     def max_wavespeed(self, U, out=None):
+        self._two()
         U = self._state(U, 'U')
         out = torch.empty(2, dtype=torch.float64, device=self.device) if out is None else out
         _check(self.lib.hweno_max_wavespeed(ctypes.byref(self.cp), _ptr(U), _ptr(self._alpha(out)),
@@ -237,7 +247,7 @@ class Solver:
 
     def rhs(self, U, V, W=None, alpha=None):
         """(L1, L2, L3, vtilde, wtilde); L3, wtilde are None in 1D."""
-        two = self.prob.dim == 2
+        two = self._two()
         U, V = self._state(U, 'U'), self._state(V, 'V')
         W = self._state(W, 'W') if two else None
         alpha = self.max_wavespeed(U) if alpha is None else self._alpha(alpha)
@@ -254,7 +264,7 @@ class Solver:
         """One SSP-RK3 step in place. ``t``: float64 device tensor (in/out).
         ``events``: optional ctypes array of 4 hipEvent_t recorded around the
         three stage launches (hweno_step_profiled)."""
-        two = self.prob.dim == 2
+        two = self._two()
         U, V = self._state(U, 'U'), self._state(V, 'V')
         W = self._state(W, 'W') if two else None
         for name, x, n in (('t', t, 1), ('dt_used', dt_used, 1), ('alpha_rec', alpha_rec, 6)):
@@ -282,7 +292,7 @@ class Solver:
         stage. ``dt_used`` / ``alpha_rec``: optional float64 device tensors of
         nsteps / nsteps x 6 values; ``events``: optional ctypes array of
         4 * nsteps hipEvent_t."""
-        two = self.prob.dim == 2
+        two = self._two()
         U, V = self._state(U, 'U'), self._state(V, 'V')
         W = self._state(W, 'W') if two else None
         nsteps = int(nsteps)
@@ -317,7 +327,7 @@ class Solver:
         """One step with the given dt (device, 1 value) and stage alphas
         (device, 6 values): the map the adjoint differentiates. In place, or
         into ``out`` = (U', V'[, W']) leaving (U, V, W) unchanged."""
-        two = self.prob.dim == 2
+        two = self._two()
         U, V = self._state(U, 'U'), self._state(V, 'V')
         W = self._state(W, 'W') if two else None
         self._scalars_ok(dt, alpha_rec)
@@ -333,7 +343,7 @@ class Solver:
 
     def adjoint_step(self, U, V, W, dt, alpha_rec, lam_in, lam_out, stages=None):
         """dJ/dX^n into ``lam_out`` (3-tuple, or 2-tuple in 1D) from dJ/dX^{n+1}."""
-        two = self.prob.dim == 2
+        two = self._two()
         U, V = self._state(U, 'U'), self._state(V, 'V')
         W = self._state(W, 'W') if two else None
         self._scalars_ok(dt, alpha_rec)
