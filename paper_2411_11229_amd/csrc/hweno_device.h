@@ -250,26 +250,32 @@ struct PointK {
   double Ac, At, Xt;       // of the modified derivative: c, S and X
 };
 
+// A linear weight that the normalisations can be divided by. The accepted ones
+// reach down to the smallest double; below 1e-60 the weight has no part in a sum
+// (gamma0 o0 against g1 (o1 + o2), where o0 / (o1 + o2) is at most about jump^4 /
+// eps), and at 1e-60 the products stay finite for jumps below 1e10.
+HWENO_HD double divisor_weight(double w) { return w > 1e-60 ? w : 1e-60; }
 // vts: the scale of the modified derivative (point_vt_scale).
 HWENO_HD PointK point_k(const Scheme& s, double lam, double vts) {
+  const double g0 = divisor_weight(s.gamma0), d0 = divisor_weight(s.d0);
   PointK k;
   k.eps = s.eps;
-  k.rho = s.g1 / s.gamma0;
-  k.rhod = s.d1 / s.d0;
-  k.K = (0.34375 - 0.5 * s.g1) / s.gamma0;
-  k.Ks = -0.09375 / (lam * s.gamma0);
-  k.m = 0.21875 / s.gamma0;
-  k.X = 0.5 * s.g1 / s.gamma0;
-  k.Ac = (0.75 - s.d1) / (s.d0 * vts);
-  k.At = -0.25 / (lam * s.d0 * vts);
-  k.Xt = s.d1 / (s.d0 * vts);
+  k.rho = s.g1 / g0;
+  k.rhod = s.d1 / d0;
+  k.K = (0.34375 - 0.5 * s.g1) / g0;
+  k.Ks = -0.09375 / (lam * g0);
+  k.m = 0.21875 / g0;
+  k.X = 0.5 * s.g1 / g0;
+  k.Ac = (0.75 - s.d1) / (d0 * vts);
+  k.At = -0.25 / (lam * d0 * vts);
+  k.Xt = s.d1 / (d0 * vts);
   return k;
 }
 // The modified derivative returned by hweno_point_diff is h v~ over this scale:
 // in FP64 the one that makes the weight Ac of c one.
 template <typename T>
 HWENO_HD double point_vt_scale(const Scheme& s) {
-  return sizeof(T) == 8 ? (0.75 - s.d1) / s.d0 : 1.0;
+  return sizeof(T) == 8 ? (0.75 - s.d1) / divisor_weight(s.d0) : 1.0;
 }
 
 template <typename T>
