@@ -823,8 +823,12 @@ __device__ __forceinline__ void xcd_tile(int& bx, int& by) {
   bx = L - by * nbx;
 }
 
+// (FP32 with walls and source: stages 2 and 3 would take 258 registers, two more
+// than leave room for a second wavefront a SIMD; within 256 one pair of them waits
+// in scratch, outside the row loop but for a split side's rows. 2048^2, two steps:
+// 1471 -> 1341 us.)
 template <class Sys, typename T, int MODE, int VAR>
-__global__ __launch_bounds__(64) void stage2d_kernel(StageArgs<T> A, Sys sy) {
+__global__ __launch_bounds__(64, sizeof(T) == 4 && VAR == (kVarWalls | kVarSource) ? 2 : 1) void stage2d_kernel(StageArgs<T> A, Sys sy) {
   constexpr bool WALLS = (VAR & kVarWalls) != 0;
   constexpr bool IFACE = (VAR & kVarIface) != 0;
   constexpr bool SOURCE = (VAR & kVarSource) != 0 && Sys::kChar && Sys::NC == 4;
