@@ -2578,15 +2578,20 @@ hweno_status dispatch(const hweno_problem* p, F&& f) {
   return p->precision == HWENO_F64 ? by_type(double{}) : by_type(float{});
 }
 
-// Occupancy of `kernel` (block size BLOCK) on the current device: blocks per
-// CU from the occupancy query (cached per kernel instance and TAG) and the CU
-// count (asked each time). False if unknown.
-template <int TAG, int BLOCK, class K>
-bool occupancy(K kernel, int* per_cu, int* cus) {
+// A kernel as a type.
+template <auto K>
+struct Kernel {
+  static constexpr auto fn = K;
+};
+// Occupancy of the kernel K (block size BLOCK) on the current device: blocks per
+// CU from the occupancy query (cached per kernel instance) and the CU count (asked
+// each time). False if unknown.
+template <auto K, int BLOCK>
+bool occupancy(int* per_cu, int* cus) {
   static std::atomic<int> per_cu_cache{0};
   int pc = per_cu_cache.load(std::memory_order_relaxed);
   if (pc <= 0) {
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, kernel, BLOCK, 0) != hipSuccess || pc <= 0)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, K, BLOCK, 0) != hipSuccess || pc <= 0)
       return false;
     per_cu_cache.store(pc, std::memory_order_relaxed);
   }
@@ -2678,9 +2683,10 @@ hweno_status launch_stage(int mode, const StageArgs<T>& A0, const Sys& sy, hipSt
     }
   } else {
     const int col_blocks = (A.nx + kXOut - 1) / kXOut;
-    auto go = [&](auto kernel, auto tile, auto tag) {
+    auto go = [&](auto kernel, auto tile) {
+      constexpr auto fn = decltype(kernel)::fn;
       int per_cu = 0, cus = 0;
-      const bool known = occupancy<decltype(tag)::value, kWave>(kernel, &per_cu, &cus);
+      const bool known = occupancy<fn, kWave>(&per_cu, &cus);
       const int forced = g_strip_rows.load(std::memory_order_relaxed);
       if constexpr (sizeof(T) == 8) {
         A.rows = known && forced <= 0 ? tile_rows(col_blocks, A.ny, cus, kTileRows) : 0;
@@ -2694,16 +2700,15 @@ hweno_status launch_stage(int mode, const StageArgs<T>& A0, const Sys& sy, hipSt
       // about one full row in all
       A.rows = forced > 0 ? forced : balanced_rows(col_blocks, A.ny, known, per_cu, cus, 1.0, 32);
       dim3 grid(col_blocks, (A.ny + A.rows - 1) / A.rows);
-      kernel<<<grid, kWave, 0, st>>>(A, sy);
+      fn<<<grid, kWave, 0, st>>>(A, sy);
     };
     auto modes = [&](auto var) {
       constexpr int V = decltype(var)::value;
-      constexpr int kT = 16 * V;   // separate occupancy cache entries
       switch (mode) {
-        case kRhs: go(stage2d_kernel<Sys, T, kRhs, V>, [](int h) { return tile_kernel<Sys, T, kRhs, V>(h); }, std::integral_constant<int, kRhs + kT>{}); break;
-        case kStage1: go(stage2d_kernel<Sys, T, kStage1, V>, [](int h) { return tile_kernel<Sys, T, kStage1, V>(h); }, std::integral_constant<int, kStage1 + kT>{}); break;
-        case kStage2: go(stage2d_kernel<Sys, T, kStage2, V>, [](int h) { return tile_kernel<Sys, T, kStage2, V>(h); }, std::integral_constant<int, kStage2 + kT>{}); break;
-        default: go(stage2d_kernel<Sys, T, kStage3, V>, [](int h) { return tile_kernel<Sys, T, kStage3, V>(h); }, std::integral_constant<int, kStage3 + kT>{}); break;
+        case kRhs: go(Kernel<stage2d_kernel<Sys, T, kRhs, V>>{}, [](int h) { return tile_kernel<Sys, T, kRhs, V>(h); }); break;
+        case kStage1: go(Kernel<stage2d_kernel<Sys, T, kStage1, V>>{}, [](int h) { return tile_kernel<Sys, T, kStage1, V>(h); }); break;
+        case kStage2: go(Kernel<stage2d_kernel<Sys, T, kStage2, V>>{}, [](int h) { return tile_kernel<Sys, T, kStage2, V>(h); }); break;
+        default: go(Kernel<stage2d_kernel<Sys, T, kStage3, V>>{}, [](int h) { return tile_kernel<Sys, T, kStage3, V>(h); }); break;
       }
     };
     bool walls = false;
@@ -2846,9 +2851,10 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
     for (int k = 0; k < 4; ++k) walls = walls || p->bc[k] == HWENO_REFLECTIVE || p->bc[k] == HWENO_DIRICHLET;
     int nstrips = 0;
     const int col_blocks = (nx + kWave - 1) / kWave;
-    auto go = [&](auto kernel, auto tile, auto tag) {
+    auto go = [&](auto kernel, auto tile) {
+      constexpr auto fn = decltype(kernel)::fn;
       int per_cu = 0, cus = 0;
-      const bool known = occupancy<decltype(tag)::value, kWave>(kernel, &per_cu, &cus);
+      const bool known = occupancy<fn, kWave>(&per_cu, &cus);
       A.rows = known ? tile_rows(col_blocks, ny + 4, cus, kVjpTileRows) : 0;
       if (A.rows > 0) {   // no strip halos
         const dim3 grid(col_blocks, (ny + 4 + A.rows - 1) / A.rows);
@@ -2857,21 +2863,19 @@ hweno_status launch_vjp(const hweno_problem* p, const Sys& sy, const Geometry& g
       }
       A.rows = balanced_rows(col_blocks, ny + 4, known, per_cu, cus, 1.0, 16, kMinStripRows);
       nstrips = (ny + 4 + A.rows - 1) / A.rows;
-      kernel<<<dim3(col_blocks, nstrips), kWave, 0, st>>>(A, sy);
+      fn<<<dim3(col_blocks, nstrips), kWave, 0, st>>>(A, sy);
     };
     if (iface) {
       if constexpr (Sys::kChar) {
         if (walls)
-          go(vjp_y_kernel<Sys, T, true, true>, vjp_y_tile_kernel<Sys, T, true, true>,
-             std::integral_constant<int, 20>{});
+          go(Kernel<vjp_y_kernel<Sys, T, true, true>>{}, vjp_y_tile_kernel<Sys, T, true, true>);
         else
-          go(vjp_y_kernel<Sys, T, false, true>, vjp_y_tile_kernel<Sys, T, false, true>,
-             std::integral_constant<int, 4>{});
+          go(Kernel<vjp_y_kernel<Sys, T, false, true>>{}, vjp_y_tile_kernel<Sys, T, false, true>);
       }
     } else if (walls) {
-      go(vjp_y_kernel<Sys, T, true>, vjp_y_tile_kernel<Sys, T, true>, std::integral_constant<int, 20>{});
+      go(Kernel<vjp_y_kernel<Sys, T, true>>{}, vjp_y_tile_kernel<Sys, T, true>);
     } else {
-      go(vjp_y_kernel<Sys, T, false>, vjp_y_tile_kernel<Sys, T, false>, std::integral_constant<int, 4>{});
+      go(Kernel<vjp_y_kernel<Sys, T, false>>{}, vjp_y_tile_kernel<Sys, T, false>);
     }
     if (check_launch() != HWENO_OK) return HWENO_EDEVICE;
     ystrip_rows = A.rows;
