@@ -13,8 +13,8 @@ from paper_2411_11229_amd import hweno as H
 def test_one_cache_entry_per_marching_kernel():
     if not shutil.which('nm'):
         pytest.skip('nm not available')
-    out = subprocess.run(['nm', '-C', H.LIB_PATH], check=True, capture_output=True, text=True).stdout
-    lines = set(line.split(' ', 2)[-1] for line in out.splitlines())
-    kernels = [n for n in lines if '__device_stub__stage2d_kernel<' in n or '__device_stub__vjp_y_kernel<' in n]
-    caches = [n for n in lines if 'occupancy<' in n and n.endswith('per_cu_cache')]
+    out = subprocess.run(['nm', H.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    names = set(line.split()[-1] for line in out.splitlines() if line)
+    kernels = [n for n in names if '__device_stub__stage2d_kernel' in n or '__device_stub__vjp_y_kernel' in n]
+    caches = [n for n in names if 'occupancy' in n and 'per_cu_cache' in n]
     assert kernels and len(caches) == len(kernels)
