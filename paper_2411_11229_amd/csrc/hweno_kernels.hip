@@ -168,11 +168,13 @@ __device__ __forceinline__ void raise_alphas(StepScalars* sc, int nslots, int se
   if (flag) atomicOr(&sc->flags, flag);
 }
 
-// Touches every 64-byte line of a kernel's arguments, all in flight at once: the
-// code's own reads of them, spread over the kernel's start, then find them in
-// the scalar cache instead of waiting for one line after the other. (us a pass:
-// 60x240 with walls, 24 stage launches, 244 -> 218; 1D Euler N = 2000, 96, 556 ->
-// 514; 512^2, 12, 377 -> 369.)
+// Touches the whole 64-byte lines of a kernel's first argument, all in flight at
+// once: the code's own reads of them, spread over the kernel's start, then find
+// them in the scalar cache instead of waiting for one line after the other. (us a
+// pass: 60x240 with walls, 24 stage launches, 244 -> 218; 1D Euler N = 2000, 96,
+// 556 -> 514; 512^2, 12, 377 -> 369.) The line begun last, with the end of that
+// argument and the system's constants, is left to those reads: with it too the
+// adjoint and small scalar grids gain 1-2%, stages with walls lose up to 0.8%.
 template <class Args>
 __device__ __forceinline__ void touch_args() {
   const volatile __attribute__((address_space(4))) unsigned* p =
