@@ -344,6 +344,7 @@ HWENO_HD void face_derivs(T um, T u0, T up, T vm, T vp, T ih, T& vR, T& vL) {
 //   D(f) = -97/1920 (f_{i-1} - f_i - f_{i+1} + f_{i+2}) - 19/960 dx (h_{i-1} - h_{i+2})
 //   D(h) = [697/5184 (f_{i-1} - f_{i+2}) - 61/192 (f_i - f_{i+1})] / dx
 //          + 37/864 (h_{i-1} + h_{i+2})
+// (The direct form, for the host checks; the kernels' is interface_flux.)
 template <typename T>
 HWENO_HD void central_corr(T fm1, T f0, T fp1, T fp2, T hm1, T hp2, T h, T ih,
                                              T& Df, T& Dh) {
@@ -351,12 +352,6 @@ HWENO_HD void central_corr(T fm1, T f0, T fp1, T fp2, T hm1, T hp2, T h, T ih,
   Df = T(-97.0 / 1920.0) * s4 - T(19.0 / 960.0) * h * (hm1 - hp2);
   Dh = (T(697.0 / 5184.0) * (fm1 - fp2) - T(61.0 / 192.0) * (f0 - fp1)) * ih +
        T(37.0 / 864.0) * (hm1 + hp2);
-}
-
-// (mixed): interface value of a mixed-derivative flux.
-template <typename T>
-HWENO_HD T mixed_face(T em1, T e0, T ep1, T ep2) {
-  return (T(7.0) * (e0 + ep1) - (em1 + ep2)) * T(1.0 / 12.0);
 }
 
 // ---------------------------------------------------------------- systems

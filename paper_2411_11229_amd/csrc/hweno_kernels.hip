@@ -1188,6 +1188,7 @@ constexpr size_t tile_lds(int H) {
 
 template <class Sys, typename T, int MODE, int VAR, int MOST>
 __global__ __launch_bounds__((MOST + 2) * kWave, MOST > kTileFew ? 3 : 2) void stage2d_tile_kernel(StageArgs<T> A, Sys sy) {
+  static_assert(sizeof(T) == 8);
   constexpr bool WALLS = (VAR & kVarWalls) != 0;
   constexpr bool IFACE = (VAR & kVarIface) != 0;
   constexpr bool SOURCE = (VAR & kVarSource) != 0 && Sys::kChar && Sys::NC == 4;
@@ -1258,25 +1259,18 @@ __global__ __launch_bounds__((MOST + 2) * kWave, MOST > kTileFew ? 3 : 2) void s
     // HWENO in y of row q: u at its top and bottom faces, w~, the LF sums there
     ce = sy.cell_eig(Ub);
     T uT[NC], uB[NC], wT[NC], wB[NC];
-    if constexpr (IFACE && sizeof(T) == 4) {
-      // mesh width 1 for the scaled derivatives
-      hweno_cell_b<1, true>(sy, s, 1.0, 1.0, ce.q, Ua, Ub, Uc, Wa, Wc, uT, uB, wt);
+    T E1[NC], E2[NC], Sw[NC], Dw[NC];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) face_derivs(Ua[c], Ub[c], Uc[c], Wa[c], Wc[c], T(1), wT[c], wB[c]);
-    } else {
-      T E1[NC], E2[NC], Sw[NC], Dw[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        E1[c] = Ub[c] - Ua[c];
-        E2[c] = Uc[c] - Ub[c];
-        Sw[c] = Wa[c] + Wc[c];
-        Dw[c] = Wa[c] - Wc[c];
-      }
-      if constexpr (IFACE)
-        hweno_cell_diff_iface<1>(sy, A.pk, ce, Ua, Ub, Uc, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
-      else
-        hweno_cell_diff<1>(sy, A.pk, ce, Ub, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
+    for (int c = 0; c < NC; ++c) {
+      E1[c] = Ub[c] - Ua[c];
+      E2[c] = Uc[c] - Ub[c];
+      Sw[c] = Wa[c] + Wc[c];
+      Dw[c] = Wa[c] - Wc[c];
     }
+    if constexpr (IFACE)
+      hweno_cell_diff_iface<1>(sy, A.pk, ce, Ua, Ub, Uc, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
+    else
+      hweno_cell_diff<1>(sy, A.pk, ce, Ub, E1, E2, Sw, Dw, uT, uB, wt, wT, wB);
     T gt[NC], tt[NC], gb[NC], tb[NC];
     const T a_y = T(ay);
     const auto qt = prim_rounded(sy, uT);
@@ -1361,10 +1355,7 @@ __global__ __launch_bounds__((MOST + 2) * kWave, MOST > kTileFew ? 3 : 2) void s
         const T sG = M(k - 1, 0) + M(k, 2), sT = M(k - 1, 1) + M(k, 3);
         const T hm = F(k - 2, 1), hp = F(k + 1, 1);
         const T g0 = F(k - 2, 0), g1 = F(k - 1, 0), g2 = F(k, 0), g3 = F(k + 1, 0);
-        if constexpr (kFluxScaled<T>)
-          interface_flux(g1 - g0, g2 - g1, g3 - g2, hm, hp, sG, sT, G[k], Tn[k]);
-        else
-          interface_flux_plain(g0, g1, g2, g3, hm, hp, sG, sT, G[k], Tn[k]);
+        interface_flux(g1 - g0, g2 - g1, g3 - g2, hm, hp, sG, sT, G[k], Tn[k]);
         X[k] = fma(T(7), F(k - 1, 2) + F(k, 2), -(F(k - 2, 2) + F(k + 1, 2)));
       }
       const unsigned idx = (unsigned)(c * A.plane + q * A.nx + col);
@@ -1513,7 +1504,7 @@ VjpScales vjp_scales(const Scheme& s, double h, double cb) {
   k.lamh = lam * h;
   k.u = 0.5 * cb / h;                    // the two halves of the LF flux
   k.a = 0.5 * cb / (h * (mu * lam * h));
-  k.o = cb / (12.0 * h);                 // (mixed_face)
+  k.o = cb / (12.0 * h);                 // (mixed)
   k.vt = point_vt_scale<T>(s) / h;
   return k;
 }
@@ -1567,7 +1558,7 @@ HWENO_HD int halo_source(int q, int R, int nstrips, int& side) {
 // Cotangents of the pointwise fluxes of a cell from those of the interfaces
 // i-3/2 .. i+3/2 (F: of the flux, halved, H: of the along-derivative flux,
 // halved and scaled, E: of the mixed one, over 12): the transpose of the central
-// correction (Cd-1)-(DfDh) and of mixed_face.
+// correction (Cd-1)-(DfDh) and of (mixed).
 template <typename T>
 __device__ __forceinline__ void point_cotangents(T F1, T F0, T Fm1, T Fm2, T H1, T H0, T Hm1, T Hm2,
                                                  T& gf, T& gh) {
