@@ -227,9 +227,11 @@ HWENO_HD void hweno_point(T um, T u0, T up, T vm, T vp, const Scheme& s,
 // Euler::jac, interface_flux) a row iteration of the FP64 2D Euler stage kernel
 // went from 1555 to 1408 VALU instructions, that of the interface basis from
 // 2826 to 2371, FP32's from 1490 to 1418: 2048^2, two steps, 2.05 -> 1.99 ms
-// (there the chip is at its power limit: 1400 W, 2.05 GHz), FP32 one step 0.737
-// -> 0.702 ms, interface basis 1000x777 0.729 -> 0.661 ms. The smoothness indicators, tau, epsilon, the weights and the
-// combinations are evaluated in double; q_l = beta_l + eps is formed directly.
+// (there the card draws 1.38-1.39 kW and its clock falls to 2.1-2.2 of 2.4 GHz),
+// FP32 one step 0.737 -> 0.702 ms, interface basis 1000x777 0.729 -> 0.661 ms.
+// (1408 became 1362 when the two warm-up rows left the FP64 loop.) The smoothness
+// indicators, tau, epsilon, the weights and the combinations are evaluated in
+// double; q_l = beta_l + eps is formed directly.
 // What FP32 does in float (everything outside hweno_point_diff) keeps the
 // textbook scaling and order of operations, lam = 1: each reordering there
 // moves the rounding of its results at the 1e-7 level, that of the time step

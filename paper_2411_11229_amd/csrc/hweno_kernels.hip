@@ -2108,7 +2108,9 @@ __global__ __launch_bounds__(64) void vjp_y_kernel(VjpYArgs<T> A, Sys sy) {
 // what the cells add to the rows below and above them after the work. A row's
 // sums are complete within the block: no halo terms. Bound by latency (the start,
 // the loads, one row's serial arithmetic) in place of the marcher's H + 4 rows
-// one after the other; measured at the rule (tile_rows).
+// one after the other; measured at the rule (tile_rows). Two wavefronts a SIMD at
+// six rows leave 256 registers: FP64 Euler waits with 32 B a lane in scratch, in
+// the interface basis with 500 B (the marcher, with 512 registers, 0 and 52 B).
 constexpr int kVjpTileRows = 6;
 constexpr int kVjpTileThreads = (kVjpTileRows + 2) * kWave;
 template <int NC, typename T>
@@ -2633,7 +2635,8 @@ int balanced_rows(long col_blocks, int rows, bool known, int per_cu, int cus, do
 // more rows, is as fast. Measured (FP64 Euler, us a stage, marcher | tile): 60x60
 // 11.2 | 7.6, 60x240 11.5 | 7.9, 240x240 13.7 | 11.0, 256x256 17.4 | 12.5, 320x256
 // 17.6 | 14.6, 385x250 18.3 | 15.2, 480x256 19.0 | 16.9; in two rounds 385x250 |
-// 18.6. The y-pass of the adjoint follows the same rule, in both precisions (FP64 Euler, us for
+// 18.6; Burgers, the marcher at its best height: 60x60 6.2 | 5.5, 240x240 7.2 |
+// 6.5, 256x256 7.4 | 6.9, 320x256 7.4 | 7.5, 480x256 8.1 | 8.2. The y-pass of the adjoint follows the same rule, in both precisions (FP64 Euler, us for
 // the adjoint of a step, three y-passes in it): 64x64 105 | 56, 128x128 109 | 57,
 // 256x256 126 | 88, 320x256 131 | 93, interface basis 209 | 172, FP32 105 | 74;
 // beyond the line 384x384 161 | 151, interface basis 254 | 281, 512x512 214 | 230.

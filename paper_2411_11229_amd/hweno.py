@@ -369,8 +369,9 @@ class Solver:
         chunks; the device skips steps once t reaches t_end. Returns
         (steps, t, dts[, alpha_recs]) with dts / alphas as device tensors.
 
-        Each chunk is one hweno_steps call: two seeding launches, then the
-        three stage kernels per step. graph=True captures one chunk as a HIP
+        Each chunk is one hweno_steps call: a seeding launch, then the three
+        stage kernels per step (a short 1D line in FP64: one launch for up to
+        64 steps). graph=True captures one chunk as a HIP
         graph and replays it (one graph launch per chunk): for sizes where
         launch overhead, not the kernels, sets the pace. The results are the
         same bit for bit."""
